@@ -160,6 +160,8 @@ def trav_kernel_name(kind: str, fused: int, arcs: int, n: int) -> str:
     if fused == 2:
         return "unfused per-phase kernels"
     seq = fused in (0, 3)
+    if kind == "wcc" and fused == 0:
+        return "k_wcc_* (hooking)"
     if kind == "kcore":
         return "k_kcore_seq" if seq else "k_kcore_fused"
     ops = {"bfs": "BfsOps", "wcc": "WccOps"}.get(kind, "SsspOps")

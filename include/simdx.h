@@ -127,6 +127,11 @@ sx_status sx_graph_info(const sx_graph *g, int32_t *n, int64_t *m, int32_t *dire
  *              smallest vertex id of the vertex's component (unique, so
  *              comparable bit for bit).  Undirected graphs only
  *              (SX_EUNSUPPORTED otherwise); the source is ignored (pass -1).
+ *              Under a policy that fixes nothing (every field but the
+ *              watchdog and kcore_tail 0) the same labels come from hooking
+ *              and pointer jumping, whose work does not grow with the
+ *              diameter: statistics then count its link phases as iterations
+ *              and the arcs and vertices these walk.
  *  SX_BP       belief propagation (Section 6: sum-product message passing,
  *              the vertex probability as metadata; Section 3.2: every vertex
  *              active, updates summed) on a binary pairwise Markov random

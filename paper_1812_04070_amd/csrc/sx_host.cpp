@@ -1041,6 +1041,39 @@ static sx_status run_traversal(sx_program *p, sx_graph *G, int src, void *d_out,
   return SX_OK;
 }
 
+// The policy leaves the schedule to the engine (every field at its default;
+// the watchdog and the k-core tail do not touch the traversals' schedule).
+static bool engine_schedules(const sx_policy &pol) {
+  return pol.direction == SX_DIR_AUTO && pol.filter == SX_FILTER_JIT && pol.bin_small == 0 && pol.bin_large == 0 &&
+         pol.online_cap == 0 && pol.fused == SX_FUSE_AUTO && pol.policy == SX_POLICY_HEURISTIC && pol.grid_wgs == 0;
+}
+
+// ----------------------------------------- components by hooking ---
+// The paper's label propagation needs an iteration per hop and its frontier
+// machinery; hooking needs six or seven launches whatever the graph (us a run,
+// propagation -> hooking: R-MAT s10 176 -> 66, s16 416 -> 64, s22 2,890 -> 165;
+// grids of side 64, 1024, 4096: 1,100 -> 79, 74,570 -> 170, 2.9 s -> 950).
+static sx_status run_wcc(sx_program *p, sx_graph *G, void *d_out, hipStream_t st, sx_run_stats *stats) {
+  WccArgs a;
+  memset(&a, 0, sizeof a);
+  a.g = G->g;
+  a.ctrl = G->w.ctrl;
+  a.par = (int *)(G->reordered ? G->state : d_out);
+  a.out = (int *)d_out;
+  a.inv = G->reordered ? G->d_inv : nullptr;
+  a.low = (unsigned *)G->w.stamp;
+  int launches = 0;
+  HIP_TRY(hipEventRecord(G->ev0, st));
+  HIP_TRY(wcc_launch(a, p->ctx->cus, st, &launches));
+  HIP_TRY(hipEventRecord(G->ev1, st));
+  sx_status s = read_ctrl(G, st);
+  if (s != SX_OK) return s;
+  float ms = 0.f;
+  HIP_TRY(hipEventElapsedTime(&ms, G->ev0, G->ev1));
+  fill_stats(G->h_ctrl, launches, ms, 0, p->ctx->wall_khz, stats);
+  return SX_OK;
+}
+
 // ------------------------------------------------------------- k-core ---
 static sx_status run_kcore(sx_program *p, sx_graph *G, void *d_out, hipStream_t st,
                            sx_run_stats *stats) {
@@ -1599,6 +1632,7 @@ extern "C" sx_status sx_run(sx_program *p, const sx_graph *gc, int32_t source, v
         if (stats) memset(stats, 0, sizeof *stats);
         return SX_OK;
       }
+      if (engine_schedules(p->pol)) return run_wcc(p, G, d_out, st, stats);
       s = run_traversal(p, G, 0, state, st, stats);
       break;
     case SX_PAGERANK:
@@ -1711,6 +1745,7 @@ extern "C" sx_status sx_run_static(sx_program *p, const sx_graph_desc *d, int32_
   const unsigned long long words = sizeof(Ctrl) / 4;
   hipLaunchKernelGGL(k_static_clear, dim3(64), dim3(256), 0, st, (unsigned *)G.w.ctrl, words);
   HIP_TRY(hipGetLastError());
+  if (algo == SX_WCC && engine_schedules(p->pol)) return run_wcc(p, &G, d_out, st, stats);
   return run_traversal(p, &G, source, d_out, st, stats);
 }
 

@@ -29,6 +29,9 @@ hipError_t weight_sum(const unsigned *w, long long m, unsigned long long *out, h
 enum : unsigned { SEQ_DONE = 6, SEQ_ERROR = 7, SEQ_LIMIT = 8 };
 const void *batch_kernel();
 
+// components by hooking; *launches = kernels enqueued
+hipError_t wcc_launch(const WccArgs &a, int cus, hipStream_t s, int *launches);
+
 hipError_t kcore_launch(const KArgs &a, int grid, hipStream_t s, bool init);
 const void *kcore_kernel();
 hipError_t kcore_seq_launch(const KArgs &a, unsigned L, int grid, hipStream_t s, bool start);

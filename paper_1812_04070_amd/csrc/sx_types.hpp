@@ -216,6 +216,16 @@ struct BpArgs {
   int iters;
 };
 
+// Connected components by hooking (sx_wcc.hip).
+struct WccArgs {
+  DevGraph g;
+  Ctrl *ctrl;
+  int *par;                     // parents (not renumbered: the output array)
+  int *out;                     // output labels, the caller's numbering
+  const int *inv;               // renumbered graph: original id -> new id, else NULL
+  unsigned *low;                // and per root the smallest original id
+};
+
 // Direction and filter choice for the next iteration (Sections 4 and 5).
 // Evaluated identically by every workgroup after a barrier in the fused
 // kernels, and by the host between launches in one-phase mode.
