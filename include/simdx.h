@@ -215,7 +215,12 @@ void sx_program_destroy(sx_program *p);
  *             the global barrier; a BFS / SSSP / WCC run enqueues first as
  *             many launches as the previous run of that algorithm on the
  *             same sx_graph needed, plus two, else 16) | 0 = auto
- *             (sequenced for BFS, SSSP and k-core, fused for PageRank)
+ *             (sequenced for BFS, SSSP and k-core, fused for PageRank; with
+ *             every other field 0 too, a BFS, or an SSSP with buckets, on a
+ *             graph of fewer than 8 arcs per vertex goes over to launches
+ *             that each advance it by a window of distances once its
+ *             frontier stays light: same results, and for BFS the same
+ *             iteration count, the levels)
  *  policy     SX_POLICY_HEURISTIC | SX_POLICY_LEARNED (MLP; needs
  *             sx_policy_load_mlp first)                                       */
 enum { SX_DIR_AUTO = 0, SX_DIR_PUSH = 1, SX_DIR_PULL = 2 };

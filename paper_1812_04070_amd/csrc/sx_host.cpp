@@ -710,10 +710,10 @@ static sx_status seq_drive(sx_graph *G, hipStream_t st, int first, int maxb, uns
     s = ctrl_error(p.h);
     if (s != SX_OK) return s;
     const unsigned ph = p.h->seq[p.L & 1].v[0];
+    if (fin_phase) *fin_phase = ph;
     if (ph == SEQ_LIMIT) return fail(SX_EHIP, "iteration limit reached (engine bug)");
     if (ph >= SEQ_DONE) {
       *fin = p.h;
-      if (fin_phase) *fin_phase = ph;
       return SX_OK;
     }
     if (L > limit) return fail(SX_EHIP, "run did not converge");
@@ -874,6 +874,28 @@ static int traversal_grid(sx_program *p, const sx_graph *G, int max_it) {
   return grid;
 }
 
+// The policy leaves the schedule to the engine (every field at its default;
+// the watchdog and the k-core tail do not touch the traversals' schedule).
+static bool engine_schedules(const sx_policy &pol) {
+  return pol.direction == SX_DIR_AUTO && pol.filter == SX_FILTER_JIT && pol.bin_small == 0 && pol.bin_large == 0 &&
+         pol.online_cap == 0 && pol.fused == SX_FUSE_AUTO && pol.policy == SX_POLICY_HEURISTIC && pol.grid_wgs == 0;
+}
+
+// Cascade (sx_cascade.hip): runs the engine schedules on graphs of fewer than
+// 8 arcs per vertex (denser ones end within the iterations below).  A BFS goes
+// over after 8 levels of a frontier that stays light (2^16 arcs) and does not
+// grow by half, an SSSP with buckets after 16 iterations (64^2 grid BFS 1.86 ->
+// 0.36 ms; random and R-MAT graphs of 3-6 arcs per vertex reach the threshold
+// in their last, light levels if at all).  The window: 64 levels, or the
+// caller's bucket width; the automatic width of 40 mean weights is for phases
+// whose fixed cost is a launch, a cascade's best is 8.
+static const int kCascadeGrid = 1024;
+static const int kCascadeAfterBfs = 8, kCascadeAfterSssp = 16;
+static const unsigned kCascadeLevels = 64;
+// launches per batch where the cascade may take over: one takes 20-80 us, so
+// the host keeps ahead with few, and few run after the end
+static const int kCascadeBatch = 16;
+
 // max_it > 0: stop the one-phase arrangement after that many iterations and
 // note where the next iteration's lists are (sx_run_iterations).
 static sx_status run_traversal(sx_program *p, sx_graph *G, int src, void *d_out, hipStream_t st,
@@ -912,6 +934,15 @@ static sx_status run_traversal(sx_program *p, sx_graph *G, int src, void *d_out,
     // 4-6 arcs per vertex lost 5-13 % to buckets from the first iteration)
     a.P.delta_after = 64;
   }
+  if (sequenced && engine_schedules(p->pol) && G->g.m < 8ll * G->g.n) {
+    if (algo == ALG_BFS) {
+      a.cascade_after = kCascadeAfterBfs;
+      a.cascade_window = kCascadeLevels;
+    } else if (algo == ALG_SSSP && a.P.delta) {
+      a.cascade_after = kCascadeAfterSssp;
+      a.cascade_window = p->ap.sssp_delta == SX_DELTA_AUTO ? std::max(1u, a.P.delta / 5) : a.P.delta;
+    }
+  }
   // every WCC vertex starts active: unless the caller forces push, the first
   // iteration pulls; a push start builds its lists with a ballot scan
   const bool pull_first = p->pol.direction == SX_DIR_PULL || (wcc && p->pol.direction == SX_DIR_AUTO);
@@ -931,9 +962,14 @@ static sx_status run_traversal(sx_program *p, sx_graph *G, int src, void *d_out,
     // few launches only cost one host round trip before the next batch)
     int &hint = G->seq_hint[algo];
     const int first = hint > 0 ? std::min(hint + kSeqHintMargin, 64) : 16;
+    unsigned phase = PH_PUSH;
     sx_status s = seq_drive(
-        G, st, first, 64, (unsigned)(8 * (long long)G->g.n + 1024),
-        [&](unsigned L) { return trav_launch(seq_kind, algo, a, (int)L, 0, grid, st); }, launches, &fin);
+        G, st, first, a.cascade_after ? kCascadeBatch : 64, (unsigned)(8 * (long long)G->g.n + 1024),
+        [&](unsigned L) {
+          return phase == PH_CASCADE ? cascade_launch(a, algo == ALG_SSSP, L, kCascadeGrid, st)
+                                     : trav_launch(seq_kind, algo, a, (int)L, 0, grid, st);
+        },
+        launches, &fin, &phase);
     if (s != SX_OK) return s;
     // Ctrl::stats word 12: the index + 1 of the launch that ended the run
     hint = (int)fin->stats.v[12];
@@ -1039,13 +1075,6 @@ static sx_status run_traversal(sx_program *p, sx_graph *G, int src, void *d_out,
     memcpy(stats->policy_y, plog.y, sizeof plog.y);
   }
   return SX_OK;
-}
-
-// The policy leaves the schedule to the engine (every field at its default;
-// the watchdog and the k-core tail do not touch the traversals' schedule).
-static bool engine_schedules(const sx_policy &pol) {
-  return pol.direction == SX_DIR_AUTO && pol.filter == SX_FILTER_JIT && pol.bin_small == 0 && pol.bin_large == 0 &&
-         pol.online_cap == 0 && pol.fused == SX_FUSE_AUTO && pol.policy == SX_POLICY_HEURISTIC && pol.grid_wgs == 0;
 }
 
 // ----------------------------------------- components by hooking ---

@@ -25,8 +25,11 @@ hipError_t trav_init(const TravArgs &a, int algo, unsigned long long mu0, int ru
                      hipStream_t s, bool pull_first = false, bool sequenced = false);
 hipError_t batch_launch(const BatchArgs &b, int grid, hipStream_t s);
 hipError_t weight_sum(const unsigned *w, long long m, unsigned long long *out, hipStream_t s);
-// phases of the sequenced mode (Ctrl::seq[..].v[0])
-enum : unsigned { SEQ_DONE = 6, SEQ_ERROR = 7, SEQ_LIMIT = 8 };
+// phases of the sequenced mode (Ctrl::seq[..].v[0]); PH_CASCADE: launches of
+// k_cascade (sx_cascade.hip) take the run on
+enum : unsigned { PH_PUSH = 0, PH_BALLOT = 1, PH_PULL_SCAN = 2, PH_PULL = 3, PH_CASCADE = 4,
+                  SEQ_DONE = 6, SEQ_ERROR = 7, SEQ_LIMIT = 8 };
+hipError_t cascade_launch(const TravArgs &a, bool weighted, unsigned L, int grid, hipStream_t s);
 const void *batch_kernel();
 
 // components by hooking; *launches = kernels enqueued

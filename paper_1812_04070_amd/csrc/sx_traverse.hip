@@ -33,6 +33,8 @@
 // the online filter built for iteration it (parity it & 1 of the region
 // arrays); slot SLOT_SCAN the lists of the last ballot scan (a rebuild of the
 // push lists, or the pull candidates).
+#include <type_traits>
+
 #include "sx_frontier.hpp"
 #include "sx_kernels.hpp"
 #include "sx_policy.hpp"
@@ -879,7 +881,6 @@ __global__ void __launch_bounds__(kBlock) k_pull_step(TravArgs a, int it) {
 // batches: no host round trip per iteration, one kernel boundary (~2.5 us on
 // MI355X, against ~6-10 us for a software barrier over a full persistent
 // grid) per phase, and each phase at the occupancy of its own registers.
-enum : unsigned { PH_PUSH = 0, PH_BALLOT = 1, PH_PULL_SCAN = 2, PH_PULL = 3 };
 // seq line: [0] phase [1] iteration [2,3] unexplored arcs [4] previous
 // frontier size [6,7] activated so far [8] t1 [9] t2 [10] pulling [11] a
 // decision is due [12] the push lists come from a ballot scan [13] the
@@ -900,6 +901,43 @@ SX_DEV void seq_store(Line &l, unsigned phase, const RunState &s, unsigned pulli
   store_relaxed(&l.v[14], s.dropped);
 }
 
+// The lists of iteration it + 1 (view `cur`) as one array, in the buffer of
+// the other parity, for k_cascade; a large vertex's later chunks become -1.
+constexpr unsigned long long kCascadeMaxArcs = 1ull << 16;
+template <class Ops>
+SX_DEV void cascade_enter(const VGrid &vg, const TravArgs &a, const RunState &s, unsigned L, const ViewRef &cur,
+                          const Totals &T, Line &out) {
+  Ctrl *C = a.w.ctrl;
+  const unsigned cs = T.cnt[BIN_SMALL], cm = T.cnt[BIN_MED], total = cs + cm + T.cnt[BIN_LARGE];
+  int *list = a.w.reg_s[s.it & 1];
+  for (unsigned i = vg.bid * kBlock + threadIdx.x; i < total; i += vg.nb * kBlock) {
+    int v;
+    if (i < cs) v = cur.small(i);
+    else if (i < cs + cm) v = cur.med(i - cs);
+    else {
+      const unsigned long long x = cur.large(i - cs - cm);
+      v = (x >> 32) == 0 ? (int)(x & 0xffffffffu) : -1;
+    }
+    list[i] = v;
+  }
+  if (vg.bid == 0 && threadIdx.x == 0) {
+    const unsigned lowest = Ops::kVote ? (unsigned)s.it + 1u : load_relaxed(&C->aux.v[(s.it + 1) % 3]);
+    for (int k = 0; k < 3; ++k) {
+      store_relaxed(&C->aux.v[8 + k], k == 0 ? total : 0u);
+      store_relaxed(&C->aux.v[12 + k], k == 0 ? lowest : 0xFFFFFFFFu);
+      store_relaxed(&C->aux.v[16 + k], 0u);
+      store_relaxed(&C->aux.v[24 + k], 0u);
+    }
+    seq_store(out, PH_CASCADE, s, 0, 0, 0);
+    store_relaxed(&out.v[16], Ops::kVote ? 1u : a.cascade_window);
+    store_relaxed(&out.v[17], total);
+    store_relaxed(&out.v[18], 0u);
+    store_relaxed(&out.v[19], (unsigned)s.it & 1u);
+    // the next run's first batch of launches ends here
+    store_relaxed(&C->stats.v[12], L + 1u);
+  }
+}
+
 // kMinWaves = 6 (the wide form, for large graphs): at least six wavefronts
 // per SIMD (80 VGPRs, a few spilled to scratch), three workgroups per CU
 // instead of two, which the latency-bound push steps of large graphs turn
@@ -907,7 +945,7 @@ SX_DEV void seq_store(Line &l, unsigned phase, const RunState &s, unsigned pulli
 // each phase's critical path, so graphs with small frontiers and thousands
 // of iterations use kMinWaves = 1 (the compiler's own choice, no spills).
 // Returns whether the launch ran a phase of an active run.
-template <class Ops>
+template <class Ops, bool kCascade>
 SX_DEV bool seq_body(const TravArgs &a, unsigned L, LdsTrav &lds, LdsPolicy &pol) {
   Ctrl *C = a.w.ctrl;
   const VGrid vg = hw_grid();
@@ -936,6 +974,11 @@ SX_DEV bool seq_body(const TravArgs &a, unsigned L, LdsTrav &lds, LdsPolicy &pol
     if (lead) seq_store(out, SEQ_ERROR, s, pulling, 0, rebuilt);
     return false;
   }
+  if (kCascade && phase == PH_CASCADE) {
+    // enqueued before the host saw that the cascade took over
+    if (vg.bid == 0 && threadIdx.x < 32) store_relaxed(&out.v[threadIdx.x], in[threadIdx.x]);
+    return false;
+  }
   seq_stall_enter(C, vg.bid);
   ViewRef ref;
   Totals T;
@@ -944,6 +987,7 @@ SX_DEV bool seq_body(const TravArgs &a, unsigned L, LdsTrav &lds, LdsPolicy &pol
     T = make_view(vg, a, (s.it + 1) % 3, (s.it + 1) & 1, lds, ref);
     // one launch per phase: the weights are staged only by a launch whose
     // decision evaluates the network
+    const unsigned nf_before = s.ps.nf_prev;
     Decision d = decide<Ops>(a, s, pulling != 0, T, &pol, vg.bid == 0, true);
     if (d.done) {
       ++s.it;
@@ -972,6 +1016,15 @@ SX_DEV bool seq_body(const TravArgs &a, unsigned L, LdsTrav &lds, LdsPolicy &pol
           const unsigned long long nb = ((unsigned long long)lo / a.P.delta + 1ull) * a.P.delta;
           s.B = nb >= 0xFFFFFFFFull ? 0xFFFFFFFFu : (unsigned)nb;
         }
+      }
+    }
+    if constexpr (kCascade) {
+      // a run still going after that many iterations with a light frontier
+      // that does not grow: a high diameter
+      if (a.cascade_after && s.it + 1 >= a.cascade_after && !pulling && !d.to_pull && !d.ballot && !s.dropped &&
+          T.mf <= kCascadeMaxArcs && T.nf <= nf_before + nf_before / 2 + 64u) {
+        cascade_enter<Ops>(vg, a, s, L, ref, T, out);
+        return true;
       }
     }
     if (!pulling) {
@@ -1028,7 +1081,7 @@ template <class Ops, int kMinWaves>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kMinWaves))) k_seq(TravArgs a, unsigned L) {
   __shared__ LdsTrav lds;
   __shared__ LdsPolicy pol;
-  if (seq_body<Ops>(a, L, lds, pol)) seq_stall_leave(a.w.ctrl, blockIdx.x);
+  if (seq_body<Ops, kMinWaves == 1 && !std::is_same<Ops, WccOps>::value>(a, L, lds, pol)) seq_stall_leave(a.w.ctrl, blockIdx.x);
 }
 
 // First state of a sequenced run, written by k_trav_init's first thread
@@ -1068,6 +1121,7 @@ SX_DEV void init_state(const VGrid &vg, const TravArgs &a, bool sssp, bool wcc =
       a.w.stamp[v] = v == a.src ? 0 : -1;
     } else {
       a.state_i[v] = v == a.src ? 0 : -1;
+      if (a.cascade_after) a.w.stamp[v] = -1;   // the cascade stamps listed vertices
     }
   }
 }
@@ -1165,6 +1219,8 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))
   a.mlp = b.mlp;
   a.wcc_inv = nullptr;
   a.xdist = nullptr;   // no expansion record in batches
+  a.cascade_after = 0;
+  a.cascade_window = 0;
   load_policy(a, pol);
   for (;;) {
     if (vg.bid == 0 && threadIdx.x == 0)

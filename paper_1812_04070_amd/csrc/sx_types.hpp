@@ -159,6 +159,11 @@ struct TravArgs {
   // c + v (unique; n + m / kChunk + 2 entries); ~0u: none.  NULL: no
   // record, every listed vertex expands.
   unsigned *xdist;
+  // sequenced runs on sparse graphs: iterations after which a light frontier
+  // may go over to the cascade (sx_cascade.hip; 0: never), and its window of
+  // distances (SSSP)
+  int cascade_after;
+  unsigned cascade_window;
 };
 
 // Batched queries (see k_batch).
