@@ -216,7 +216,7 @@ void sx_program_destroy(sx_program *p);
  *             many launches as the previous run of that algorithm on the
  *             same sx_graph needed, plus two, else 16) | 0 = auto
  *             (sequenced for BFS, SSSP and k-core, fused for PageRank; with
- *             every other field 0 too, a BFS, or an SSSP with buckets, on a
+ *             every other field but policy 0 too, a BFS, or an SSSP with buckets, on a
  *             graph of fewer than 8 arcs per vertex goes over to launches
  *             that each advance it by a window of distances once its
  *             frontier stays light: same results, and for BFS the same

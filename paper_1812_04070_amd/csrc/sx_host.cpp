@@ -875,10 +875,11 @@ static int traversal_grid(sx_program *p, const sx_graph *G, int max_it) {
 }
 
 // The policy leaves the schedule to the engine (every field at its default;
-// the watchdog and the k-core tail do not touch the traversals' schedule).
+// the watchdog and the k-core tail do not touch the traversals' schedule, and
+// the learned network is asked about heavy frontiers only).
 static bool engine_schedules(const sx_policy &pol) {
   return pol.direction == SX_DIR_AUTO && pol.filter == SX_FILTER_JIT && pol.bin_small == 0 && pol.bin_large == 0 &&
-         pol.online_cap == 0 && pol.fused == SX_FUSE_AUTO && pol.policy == SX_POLICY_HEURISTIC && pol.grid_wgs == 0;
+         pol.online_cap == 0 && pol.fused == SX_FUSE_AUTO && pol.grid_wgs == 0;
 }
 
 // Cascade (sx_cascade.hip): runs the engine schedules on graphs of fewer than
@@ -1661,7 +1662,7 @@ extern "C" sx_status sx_run(sx_program *p, const sx_graph *gc, int32_t source, v
         if (stats) memset(stats, 0, sizeof *stats);
         return SX_OK;
       }
-      if (engine_schedules(p->pol)) return run_wcc(p, G, d_out, st, stats);
+      if (engine_schedules(p->pol) && p->pol.policy == SX_POLICY_HEURISTIC) return run_wcc(p, G, d_out, st, stats);
       s = run_traversal(p, G, 0, state, st, stats);
       break;
     case SX_PAGERANK:
@@ -1774,7 +1775,8 @@ extern "C" sx_status sx_run_static(sx_program *p, const sx_graph_desc *d, int32_
   const unsigned long long words = sizeof(Ctrl) / 4;
   hipLaunchKernelGGL(k_static_clear, dim3(64), dim3(256), 0, st, (unsigned *)G.w.ctrl, words);
   HIP_TRY(hipGetLastError());
-  if (algo == SX_WCC && engine_schedules(p->pol)) return run_wcc(p, &G, d_out, st, stats);
+  if (algo == SX_WCC && engine_schedules(p->pol) && p->pol.policy == SX_POLICY_HEURISTIC)
+    return run_wcc(p, &G, d_out, st, stats);
   return run_traversal(p, &G, source, d_out, st, stats);
 }
 
