@@ -160,7 +160,8 @@ typedef enum { SX_BFS = 0, SX_SSSP = 1, SX_KCORE = 2, SX_PAGERANK = 3, SX_WCC = 
  * region).  Results are identical for any
  * value; it changes the work and the iteration count only.  Used by the
  * sequenced arrangement (SX_FUSE_AUTO / SX_SEQUENCED); the persistent and
- * unfused arrangements and batches relax without buckets, and a run that
+ * unfused arrangements and batches relax without buckets (a batch under a
+ * policy that fixes nothing widens its steps by itself, see fused), and a run that
  * switches to pull steps drops the buckets from then on. */
 typedef struct {
   sx_algo algo;
@@ -220,7 +221,7 @@ void sx_program_destroy(sx_program *p);
  *             graph of fewer than 8 arcs per vertex goes over to launches
  *             that each advance it by a window of distances once its
  *             frontier stays light: same results, and for BFS the same
- *             iteration count, the levels)
+ *             iteration count, the levels; so do a batch's queries)
  *  policy     SX_POLICY_HEURISTIC | SX_POLICY_LEARNED (MLP; needs
  *             sx_policy_load_mlp first)                                       */
 enum { SX_DIR_AUTO = 0, SX_DIR_PUSH = 1, SX_DIR_PULL = 2 };

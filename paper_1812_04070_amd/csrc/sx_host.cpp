@@ -891,8 +891,6 @@ static bool engine_schedules(const sx_policy &pol) {
 // caller's bucket width; the automatic width of 40 mean weights is for phases
 // whose fixed cost is a launch, a cascade's best is 8.
 static const int kCascadeGrid = 1024;
-static const int kCascadeAfterBfs = 8, kCascadeAfterSssp = 16;
-static const unsigned kCascadeLevels = 64;
 // launches per batch where the cascade may take over: one takes 20-80 us, so
 // the host keeps ahead with few, and few run after the end
 static const int kCascadeBatch = 16;
@@ -935,7 +933,7 @@ static sx_status run_traversal(sx_program *p, sx_graph *G, int src, void *d_out,
     // 4-6 arcs per vertex lost 5-13 % to buckets from the first iteration)
     a.P.delta_after = 64;
   }
-  if (sequenced && engine_schedules(p->pol) && G->g.m < 8ll * G->g.n) {
+  if (sequenced && engine_schedules(p->pol) && G->g.m < 8ll * G->g.n && G->g.m >= 4) {
     if (algo == ALG_BFS) {
       a.cascade_after = kCascadeAfterBfs;
       a.cascade_window = kCascadeLevels;
@@ -1531,6 +1529,8 @@ extern "C" sx_status sx_run_batch(sx_ctx *ctx, const sx_query *q, int32_t nq, co
   b.nq = nq;
   b.nteams = nteams;
   b.team = team;
+  // (bin thresholds a configuration sets are the level phases' only)
+  b.cascade = !pol || engine_schedules(*pol) ? 1 : 0;
   // device-side query table, order (largest expected time first), stats
   std::vector<BatchQuery> hq((size_t)nq);
   std::vector<std::pair<double, int>> key((size_t)nq);

@@ -35,7 +35,7 @@
 // push lists, or the pull candidates).
 #include <type_traits>
 
-#include "sx_frontier.hpp"
+#include "sx_cascade.hpp"
 #include "sx_kernels.hpp"
 #include "sx_policy.hpp"
 
@@ -707,6 +707,102 @@ SX_DEV bool entry_done(Ctrl *C) {
   return e == EXIT_DONE || e == EXIT_LIMIT || e == EXIT_ERROR;
 }
 
+// ----------------------------------------------------------- cascade ---
+// Whether a run goes over to the cascade after iteration s.it: it has run for
+// a while and its frontier is light and does not grow: a high diameter.
+constexpr unsigned long long kCascadeMaxArcs = 1ull << 16;
+SX_DEV bool cascade_due(const TravArgs &a, const RunState &s, bool pulling, const Decision &d, const Totals &T,
+                        unsigned nf_before) {
+  return a.cascade_after && s.it + 1 >= a.cascade_after && !pulling && !d.to_pull && !d.ballot && !s.dropped &&
+         T.mf <= kCascadeMaxArcs && T.nf <= nf_before + nf_before / 2 + 64u;
+}
+
+// The lists of iteration it + 1 (view `cur`) as one array, in the buffer of
+// the other parity; a large vertex's later chunks become -1.  Returns its
+// length.
+SX_DEV unsigned cascade_list(const VGrid &vg, const TravArgs &a, const RunState &s, const ViewRef &cur,
+                             const Totals &T) {
+  const unsigned cs = T.cnt[BIN_SMALL], cm = T.cnt[BIN_MED], total = cs + cm + T.cnt[BIN_LARGE];
+  int *list = a.w.reg_s[s.it & 1];
+  for (unsigned i = vg.bid * kBlock + threadIdx.x; i < total; i += vg.nb * kBlock) {
+    int v;
+    if (i < cs) v = cur.small(i);
+    else if (i < cs + cm) v = cur.med(i - cs);
+    else {
+      const unsigned long long x = cur.large(i - cs - cm);
+      v = (x >> 32) == 0 ? (int)(x & 0xffffffffu) : -1;
+    }
+    list[i] = v;
+  }
+  return total;
+}
+// The first step's control words (one thread).
+SX_DEV void cascade_words(Ctrl *C, unsigned total, unsigned lowest) {
+  for (int k = 0; k < 3; ++k) {
+    store_relaxed(&C->aux.v[8 + k], k == 0 ? total : 0u);
+    store_relaxed(&C->aux.v[12 + k], k == 0 ? lowest : 0xFFFFFFFFu);
+    store_relaxed(&C->aux.v[16 + k], 0u);
+    store_relaxed(&C->aux.v[24 + k], 0u);
+  }
+}
+
+// The cascade over a team of workgroups, a step per barrier.  Returns
+// EXIT_DONE, EXIT_ERROR, or EXIT_SWITCH when a BFS goes back to its levels
+// (s.it: the level of the listed vertices).
+template <class Ops>
+SX_DEV int cascade_loop(const VGrid &vg, const TravArgs &a, GridBarrier &bar, LdsCas<Ops::kWeighted> &S,
+                        RunState &s, const ViewRef &cur, const Totals &T) {
+  Ctrl *C = a.w.ctrl;
+  const int t = threadIdx.x;
+  const bool lead = vg.bid == 0 && t == 0;
+  unsigned before = cascade_list(vg, a, s, cur, T), window = 1u;
+  if constexpr (Ops::kWeighted) {
+    // a window of 8 mean weights, of the same 512 arcs in every workgroup (the
+    // smallest listed distance is not kept without buckets: 0 makes the first
+    // step's window end low, and the step then carries what lies beyond it)
+    if (t == 0) S.edges = 0ull;
+    __syncthreads();
+    const long long sum = wave_sum_ll((long long)a.g.w[a.g.m * t / kBlock]);
+    if (lane_id() == 0) atomicAdd(&S.edges, (unsigned long long)sum);
+    __syncthreads();
+    const unsigned long long mean8 = S.edges / (kBlock / 8);
+    window = mean8 < 1 ? 1u : mean8 > 0x7FFFFFFFull ? 0x7FFFFFFFu : (unsigned)mean8;
+    __syncthreads();
+  }
+  if (lead) cascade_words(C, before, Ops::kWeighted ? 0u : (unsigned)s.it + 1u);
+  // stamps: every step's smallest distance is above the last one's, so no two
+  // steps of a run share one, also where a BFS comes back here
+  const unsigned from = (unsigned)s.it;
+  unsigned par = from & 1u;
+  if (!bar.sync()) return EXIT_ERROR;
+  for (unsigned step = 0;; ++step) {
+    if (t < 32) S.in[t] = load_relaxed(&C->aux.v[t]);
+    cas_begin(S);
+    __syncthreads();
+    const unsigned now = step % 3, nxt = (step + 1) % 3;
+    const unsigned cnt = S.in[8 + now], lowest = S.in[12 + now], left = S.in[16 + now], hubs = S.in[24 + now];
+    if (cnt + hubs == 0) {
+      if (!Ops::kWeighted) cas_levels<kBlock>(vg, a);
+      return EXIT_DONE;
+    }
+    if (!Ops::kWeighted && cnt > kCasMaxList && left == 0) {
+      if (lead) store_relaxed(&C->stats.v[6], lowest);
+      s.it = (int)lowest;
+      return EXIT_SWITCH;
+    }
+    if (!Ops::kWeighted) window = cas_window(window, cnt, before, a.cascade_window);
+    const unsigned B = lowest + window < lowest ? 0xFFFFFFFFu : lowest + window;
+    before = cnt;
+    if (vg.bid == 0) {
+      cas_clear(C, step, t);
+      if (Ops::kWeighted && t == 4) atomic_add_u32(&C->stats.v[6], 1u);
+    }
+    cascade_step<Ops::kWeighted, kBlock>(vg, a, S, cnt, hubs, B, par, nxt, (int)(0x40000000u | (from + step)));
+    par ^= 1u;
+    if (!bar.sync()) return EXIT_ERROR;
+  }
+}
+
 // ------------------------------------------------ one query, in a loop ---
 // The iteration loop of one query over a (virtual) grid synchronised by
 // `bar`.  kDir 0 / 1: the push / pull kernel of selective fusion -- only that
@@ -714,9 +810,10 @@ SX_DEV bool entry_done(Ctrl *C) {
 // (EXIT_SWITCH) so that the host launches the other kernel; kDir 2: both
 // directions, switching in place (all fusion and the batched kernel).
 // Returns the exit reason.
-template <class Ops, int kDir, bool kDedup = true>
+// `cas` (the batched kernel): LDS for a run that goes over to the cascade.
+template <class Ops, int kDir, bool kDedup = true, class Cas = int>
 SX_DEV int run_loop(const VGrid &vg, const TravArgs &a, GridBarrier &bar, LdsTrav &lds,
-                    LdsPolicy &pol, RunState &s, bool &pulling, bool &rebuilt) {
+                    LdsPolicy &pol, RunState &s, bool &pulling, bool &rebuilt, Cas *cas = nullptr) {
   constexpr bool both = kDir == 2;
   Ctrl *C = a.w.ctrl;
   ViewRef ref;
@@ -751,9 +848,24 @@ SX_DEV int run_loop(const VGrid &vg, const TravArgs &a, GridBarrier &bar, LdsTra
         push_phase<Ops, kDedup>(vg, a, s.P, ops, s.it, ref, T, lds);
         if (!bar.sync()) return EXIT_ERROR;
         T = make_view(vg, a, (s.it + 1) % 3, (s.it + 1) & 1, lds, ref);
+        const unsigned nf_before = s.ps.nf_prev;
         Decision d = decide<Ops>(a, s, false, T, &pol, vg.bid == 0);
         rebuilt = false;
         if (d.done) { ++s.it; return s.it >= a.P.max_iters ? EXIT_LIMIT : EXIT_DONE; }
+        if constexpr (!std::is_same<Cas, int>::value) {
+          if (cascade_due(a, s, pulling, d, T, nf_before)) {
+            const int r = cascade_loop<Ops>(vg, a, bar, *cas, s, ref, T);
+            if (r != EXIT_SWITCH) return r;
+            // a long frontier: its lists from the depths, then level by level
+            Ops at = make_ops<Ops>(a, s.it - 1);
+            ballot_next(vg, a, s.P, at, s.it - 1, lds);
+            if (!bar.sync()) return EXIT_ERROR;
+            T = make_view(vg, a, SLOT_SCAN, s.it & 1, lds, ref);
+            if (!scan_fits(a, T)) return EXIT_ERROR;
+            rebuilt = true;
+            continue;
+          }
+        }
         if (d.to_pull) {
           ++s.it;
           pulling = true;
@@ -901,33 +1013,14 @@ SX_DEV void seq_store(Line &l, unsigned phase, const RunState &s, unsigned pulli
   store_relaxed(&l.v[14], s.dropped);
 }
 
-// The lists of iteration it + 1 (view `cur`) as one array, in the buffer of
-// the other parity, for k_cascade; a large vertex's later chunks become -1.
-constexpr unsigned long long kCascadeMaxArcs = 1ull << 16;
+// Hand the run over to k_cascade's launches.
 template <class Ops>
 SX_DEV void cascade_enter(const VGrid &vg, const TravArgs &a, const RunState &s, unsigned L, const ViewRef &cur,
                           const Totals &T, Line &out) {
   Ctrl *C = a.w.ctrl;
-  const unsigned cs = T.cnt[BIN_SMALL], cm = T.cnt[BIN_MED], total = cs + cm + T.cnt[BIN_LARGE];
-  int *list = a.w.reg_s[s.it & 1];
-  for (unsigned i = vg.bid * kBlock + threadIdx.x; i < total; i += vg.nb * kBlock) {
-    int v;
-    if (i < cs) v = cur.small(i);
-    else if (i < cs + cm) v = cur.med(i - cs);
-    else {
-      const unsigned long long x = cur.large(i - cs - cm);
-      v = (x >> 32) == 0 ? (int)(x & 0xffffffffu) : -1;
-    }
-    list[i] = v;
-  }
+  const unsigned total = cascade_list(vg, a, s, cur, T);
   if (vg.bid == 0 && threadIdx.x == 0) {
-    const unsigned lowest = Ops::kVote ? (unsigned)s.it + 1u : load_relaxed(&C->aux.v[(s.it + 1) % 3]);
-    for (int k = 0; k < 3; ++k) {
-      store_relaxed(&C->aux.v[8 + k], k == 0 ? total : 0u);
-      store_relaxed(&C->aux.v[12 + k], k == 0 ? lowest : 0xFFFFFFFFu);
-      store_relaxed(&C->aux.v[16 + k], 0u);
-      store_relaxed(&C->aux.v[24 + k], 0u);
-    }
+    cascade_words(C, total, Ops::kVote ? (unsigned)s.it + 1u : load_relaxed(&C->aux.v[(s.it + 1) % 3]));
     seq_store(out, PH_CASCADE, s, 0, 0, 0);
     store_relaxed(&out.v[16], Ops::kVote ? 1u : a.cascade_window);
     store_relaxed(&out.v[17], total);
@@ -1019,10 +1112,7 @@ SX_DEV bool seq_body(const TravArgs &a, unsigned L, LdsTrav &lds, LdsPolicy &pol
       }
     }
     if constexpr (kCascade) {
-      // a run still going after that many iterations with a light frontier
-      // that does not grow: a high diameter
-      if (a.cascade_after && s.it + 1 >= a.cascade_after && !pulling && !d.to_pull && !d.ballot && !s.dropped &&
-          T.mf <= kCascadeMaxArcs && T.nf <= nf_before + nf_before / 2 + 64u) {
+      if (cascade_due(a, s, pulling != 0, d, T, nf_before)) {
         cascade_enter<Ops>(vg, a, s, L, ref, T, out);
         return true;
       }
@@ -1188,7 +1278,7 @@ __global__ void k_trav_init(TravArgs a, int algo, unsigned long long mu0, unsign
 // so a 6-level R-MAT query and a 4,000-level grid query overlap.
 template <class Ops>
 SX_DEV bool batch_query(const VGrid &vg, const TravArgs &a, GridBarrier &bar, LdsTrav &lds,
-                        LdsPolicy &pol, unsigned long long mu0) {
+                        LdsPolicy &pol, LdsCas<Ops::kWeighted> &cas, unsigned long long mu0) {
   RunState s;
   s.it = 0;
   s.mu = mu0;
@@ -1196,7 +1286,7 @@ SX_DEV bool batch_query(const VGrid &vg, const TravArgs &a, GridBarrier &bar, Ld
   s.ps.reached = 0;
   s.P = a.P;
   bool pulling = a.P.direction == 2, rebuilt = false;
-  const int r = run_loop<Ops, 2, false>(vg, a, bar, lds, pol, s, pulling, rebuilt);
+  const int r = run_loop<Ops, 2, false>(vg, a, bar, lds, pol, s, pulling, rebuilt, &cas);
   finish(vg, a.w.ctrl, r, s, false);
   if (r == EXIT_ERROR) return false;
   return bar.sync();
@@ -1207,6 +1297,7 @@ SX_DEV bool batch_query(const VGrid &vg, const TravArgs &a, GridBarrier &bar, Ld
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) k_batch(BatchArgs b) {
   __shared__ LdsTrav lds;
   __shared__ LdsPolicy pol;
+  __shared__ union { LdsCas<true> sssp; LdsCas<false> bfs; } cas;
   const unsigned team = blockIdx.x / (unsigned)b.team;
   const VGrid vg{blockIdx.x % (unsigned)b.team, (unsigned)b.team};
   if (team >= (unsigned)b.nteams) return;
@@ -1219,8 +1310,8 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))
   a.mlp = b.mlp;
   a.wcc_inv = nullptr;
   a.xdist = nullptr;   // no expansion record in batches
-  a.cascade_after = 0;
-  a.cascade_window = 0;
+  a.cascade_window = kCascadeLevels;
+
   load_policy(a, pol);
   for (;;) {
     if (vg.bid == 0 && threadIdx.x == 0)
@@ -1234,6 +1325,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))
     a.src = Q.src;
     a.P.max_iters = Q.g.n + 2;
     const bool sssp = Q.algo == 1;
+    a.cascade_after = b.cascade && Q.g.m < 8ll * Q.g.n && Q.g.m >= 4 ? (sssp ? kCascadeAfterSssp : kCascadeAfterBfs) : 0;
     init_state(vg, a, sssp);
     // the previous query's statistics were read before the barrier above
     if (vg.bid < (unsigned)kStatLines && threadIdx.x == 0) {
@@ -1250,8 +1342,8 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))
     if (vg.bid == 0 && threadIdx.x < 64) init_source(a, vg.nb);
     if (!bar.sync()) break;
     const unsigned long long mu0 = (unsigned long long)(Q.g.m - degree_of(Q.g.off, Q.src));
-    const bool ok = sssp ? batch_query<SsspOps>(vg, a, bar, lds, pol, mu0)
-                         : batch_query<BfsOps>(vg, a, bar, lds, pol, mu0);
+    const bool ok = sssp ? batch_query<SsspOps>(vg, a, bar, lds, pol, cas.sssp, mu0)
+                         : batch_query<BfsOps>(vg, a, bar, lds, pol, cas.bfs, mu0);
     if (vg.bid == 0 && threadIdx.x == 0) {
       BatchStat &r = b.stats[b.order[qi]];
       r.iterations = (int)load_relaxed(&C->stats.v[6]);

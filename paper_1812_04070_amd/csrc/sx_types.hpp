@@ -166,6 +166,11 @@ struct TravArgs {
   unsigned cascade_window;
 };
 
+// Iterations after which a BFS / an SSSP may go over to the cascade, and the
+// levels a BFS step takes at most.
+constexpr int kCascadeAfterBfs = 8, kCascadeAfterSssp = 16;
+constexpr unsigned kCascadeLevels = 64;
+
 // Batched queries (see k_batch).
 struct BatchQuery {
   DevGraph g;
@@ -188,6 +193,7 @@ struct BatchArgs {
   Params P;
   const float *mlp;
   BatchStat *stats;             // [nq]
+  int cascade;                  // 1: queries on sparse graphs may go over to the cascade
 };
 
 struct KArgs {

@@ -123,3 +123,31 @@ def test_cascade_static_and_overflow(engine):
     out, _ = engine.run(dp, sx.SX_BFS, 0)
     np.testing.assert_array_equal(engine.to_host(dp, sx.SX_BFS, out), np.arange(60))
     dp.close()
+
+
+@pytest.mark.parametrize("team", [1, 3, 32])
+def test_cascade_batch(engine, team):
+    """Queries of a batch on the same graphs, by teams of 1 to 32 workgroups;
+    each graph is queried several times, so workspaces carry earlier stamps."""
+    import torch
+    loaded, queries, outs, refs = [], [], [], []
+    for name, make in GRAPHS:
+        g = make()
+        dg = engine.load(g)
+        loaded.append(dg)
+        for k, s in enumerate((0, g.n - 1 if not g.directed else 1, 0)):
+            algo = sx.SX_BFS if k == 2 or (k + len(loaded)) % 2 else sx.SX_SSSP
+            outs.append(torch.empty(g.n, dtype=torch.int32, device="cuda"))
+            queries.append((dg.handle, algo, s, outs[-1].data_ptr()))
+            refs.append((name, algo, s, oracle.bfs_g(g, s) if algo == sx.SX_BFS else oracle.sssp_g(g, s)))
+    cfg = sx.sx_batch_config(team, 0, 0)
+    for rep in range(2):
+        announce(f"cascade batch team={team} rep {rep}")
+        _, stats = sx.sx_run_batch(engine.ctx, queries, cfg=cfg, stream=engine.stream())
+        for (name, algo, s, ref), out, st in zip(refs, outs, stats):
+            got = out.cpu().numpy().view(ref.dtype)
+            np.testing.assert_array_equal(got, ref, err_msg=f"{name} algo={algo} src={s}")
+            if algo == sx.SX_BFS:
+                assert st["iterations"] == ref.max() + 1
+    for dg in loaded:
+        dg.close()
