@@ -570,9 +570,9 @@ extern "C" sx_status sx_program_set_policy(sx_program *p, const sx_policy *pol) 
 // on every level (4096^2 grid BFS: 160 ms wide, 47 ms on the 2048^2 grid).
 static const long long kBigGraphArcs = 1ll << 25;
 
-static int persistent_grid(sx_ctx *ctx, const void *kernel, int requested) {
+static int persistent_grid(sx_ctx *ctx, const void *kernel, int requested, int block = kBlock) {
   int per = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, kBlock, 0) != hipSuccess || per < 1)
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, block, 0) != hipSuccess || per < 1)
     per = 1;
   int grid = per * ctx->cus;
   grid = std::min(grid, kMaxGrid);
@@ -1189,7 +1189,7 @@ static sx_status run_pagerank(sx_program *p, sx_graph *G, void *d_out, hipStream
     return SX_OK;
   }
   const bool conv = p->ap.pr_tol > 0.f;
-  const int grid = persistent_grid(p->ctx, pagerank_kernel(conv), p->pol.grid_wgs);
+  const int grid = persistent_grid(p->ctx, pagerank_kernel(conv), p->pol.grid_wgs, kPagerankBlock);
   PrArgs a;
   memset(&a, 0, sizeof a);
   a.g = G->g;
@@ -1894,8 +1894,8 @@ extern "C" sx_status sx_kernel_info_get(sx_ctx *ctx, const char *name, sx_kernel
       {"kcore_fused", kcore_kernel(), true},
       {"kcore_tail", kcore_tail_kernel(), false, kTailThreads},
       {"kcore_seq", kcore_seq_kernel(), false},
-      {"pagerank_fused", pagerank_kernel(), true},
-      {"pagerank_until_stable", pagerank_kernel(true), true},
+      {"pagerank_fused", pagerank_kernel(), true, kPagerankBlock},
+      {"pagerank_until_stable", pagerank_kernel(true), true, kPagerankBlock},
       {"pagerank_push_tail", pagerank_push_kernel(), true},
       {"bp_fused", bp_kernel(), true},
       {"batch", batch_kernel(), true},
@@ -1913,7 +1913,7 @@ extern "C" sx_status sx_kernel_info_get(sx_ctx *ctx, const char *name, sx_kernel
     out->wgs_per_cu = per;
     out->cus = ctx->cus;
     // the k-core tail runs one workgroup
-    out->grid_wgs = t.block == kBlock ? std::min(per * ctx->cus, kMaxGrid) : 1;
+    out->grid_wgs = t.k == kcore_tail_kernel() ? 1 : std::min(per * ctx->cus, kMaxGrid);
     return SX_OK;
   }
   return fail(SX_EINVAL, "unknown kernel name '%s'", name);

@@ -52,6 +52,7 @@ hipError_t pagerank_launch(const PrArgs &a, int grid, hipStream_t s);
 // conv: the pull kernel of the run to convergence (launched after k_pr_init
 // by pagerank_launch); its push tail is a kernel of its own
 const void *pagerank_kernel(bool conv = false);
+constexpr int kPagerankBlock = 1024;   // its threads per workgroup
 hipError_t pagerank_push_launch(const PrArgs &a, int grid, hipStream_t s);
 const void *pagerank_push_kernel();
 

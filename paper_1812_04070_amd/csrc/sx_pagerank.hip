@@ -42,8 +42,10 @@
 // the fixed point (Sherman-Morrison on the rank-one dangling term).  So the
 // tail ends with one normalisation to sum 1.  A pending change at most thr
 // per vertex leaves an L1 error of at most n thr / (1 - d).
-#include "sx_frontier.hpp"
+#include <type_traits>
+
 #include "sx_kernels.hpp"
+#include "sx_rows.hpp"
 
 namespace sx {
 
@@ -70,29 +72,31 @@ SX_DEV float atomic_exch_f32(float *p, float v) {
 // Dangling mass D_t from the per-workgroup partials of iteration t.
 SX_DEV float dangling_total(const float *part, int nparts, float *lds) {
   CSum a{0.f, 0.f};
-  for (int i = threadIdx.x; i < nparts; i += kBlock) a = cmerge(a, CSum{part[2 * i], part[2 * i + 1]});
-  a = wg_merge(a, lds);
+  for (int i = threadIdx.x; i < nparts; i += kPullBlock) a = cmerge(a, CSum{part[2 * i], part[2 * i + 1]});
+  a = pull_merge1(a, lds);
   return a.s + a.c;
 }
 
-// Binned vertex lists (by in-degree, one item per vertex), built once by the
-// ballot filter into slot SLOT_SCAN, parity 0.
-SX_DEV void pr_lists(const PrArgs &a, LdsPr &lds) {
-  const int *io = a.g.in_off;
-  auto pred = [](int v) { (void)v; return true; };
-  auto deg = [&](int v) { return io[v + 1] - io[v]; };
-  auto ident = [](int i) { return i; };
-  const VGrid vg = hw_grid();
-  ballot_fill(vg, a.g.n, pred, deg, ident, a.P, 0x7fffffff, a.w.bits, regions(a.w, 0, vg.nb),
-              a.w.rec + SLOT_SCAN, lds.ball);
+// LDS of the pull kernels.
+struct LdsPull {
+  LdsRows rows;
+  float f[2 * kPullWaves * 4];
+};
+
+// The rows (in-arcs) of the run, built by its first two phases.  False when a
+// barrier failed.
+SX_DEV bool pr_rows(const PrArgs &a, const VGrid &vg, GridBarrier &bar, LdsPull &lds, Rows &r) {
+  rows_count(vg, a.w, a.g.n, a.g.in_off, a.P, lds.rows);
+  if (!bar.sync()) return false;
+  r = rows_place(vg, a.w, a.g.n, a.g.in_off, a.g.off, a.P, lds.rows);
+  return bar.sync();
 }
 
 // One vertex's new value from its in-arc sum; returns the dangling share.
-SX_DEV void pr_finish_vertex(const PrArgs &a, int v, CSum s, float D, bool last, float *dst,
+SX_DEV void pr_finish_vertex(const PrArgs &a, int v, int od, CSum s, float D, bool last, float *dst,
                              CSum &dang) {
   const float d = a.P.pr_d;
   const float r = a.base_teleport + d * ((s.s + s.c) + D * a.inv_n);
-  const int od = a.g.off[v + 1] - a.g.off[v];
   if (last) a.rank[v] = r;
   else if (od > 0) dst[v] = r / (float)od;
   if (od == 0) cadd(dang, r);
@@ -100,42 +104,40 @@ SX_DEV void pr_finish_vertex(const PrArgs &a, int v, CSum s, float D, bool last,
 
 // The contributions of the first kHotPr vertices, copied into LDS by every
 // workgroup at the start of each pull iteration.  After the degree-ordered
-// renumbering they are the highest-degree sources (the first 8,192 of
-// directed R-MAT s24 send 21 % of its arcs), and a gather served by LDS is
-// one request fewer at the L2, whose request rate bounds the pull more than
-// its misses do (s24: 36.3 -> 34.4 ms for 20 iterations, the same bits;
-// 16,384 entries cost a workgroup per CU and gained nothing).
-constexpr int kHotPr = 8192;
+// renumbering they are the highest-degree sources (the first 39,936 of
+// directed R-MAT s24 send 39 % of its arcs), and a gather served by LDS is
+// one request fewer at the L2, which serves about 200 G scattered requests a
+// second on MI355X and bounds the pull of a large graph.  One workgroup per CU,
+// so that the copy may take nearly all of its LDS.
+constexpr int kHotPr = 39936;
 
 // Stage src[0, nhot) into hot (every thread of the workgroup).
 SX_DEV void stage_hot(float *hot, const float *src, int nhot) {
-  for (int i = threadIdx.x; i < nhot; i += kBlock) hot[i] = src[i];
+  for (int i = threadIdx.x; i < nhot; i += kPullBlock) hot[i] = src[i];
   __syncthreads();
 }
 
-// s += src[ii[e]] for e = e0, e0 + stride, ... < end, in that order (an
-// index below nhot reads the LDS copy hot instead).  The indices and
-// contributions of kIlp consecutive terms are loaded before any of them is
-// added, so a lane has kIlp gathers in flight instead of one; the additions
-// keep their order, so the sum is the same bits.
-SX_DEV void gather(CSum &s, const float *src, const int *ii, int e0, int end, int stride,
-                   long long &edges, const float *hot, int nhot) {
-  int e = e0;
-  for (; e + (kIlp - 1) * stride < end; e += kIlp * stride) {
+// s += src[ii[beg + e]] for e = e0, e0 + stride, ... < len, in that order (an
+// index below nhot reads the LDS copy hot instead), kIlp ids and then kIlp
+// gathers of a lane in flight.  Whole wavefronts; a place past the row's end
+// reads the row's first id and adds zero, which changes neither part of a
+// compensated sum.
+SX_DEV void gather(CSum &s, const float *src, const int *ii, int beg, int e0, int len, int stride,
+                   const float *hot, int nhot) {
+  for (int e = e0; ballot(e < len); e += kIlp * stride) {
     int u[kIlp];
     float x[kIlp];
 #pragma unroll
-    for (int r = 0; r < kIlp; ++r) u[r] = ii[e + r * stride];
+    for (int r = 0; r < kIlp; ++r) u[r] = ii[beg + (e + r * stride < len ? e + r * stride : 0)];
 #pragma unroll
-    for (int r = 0; r < kIlp; ++r) x[r] = u[r] < nhot ? hot[u[r]] : src[u[r]];
+    for (int r = 0; r < kIlp; ++r) {
+      const bool ok = e + r * stride < len;
+      const int i = ok ? u[r] : 0;
+      x[r] = i < nhot ? hot[i] : src[i];
+      x[r] = ok ? x[r] : 0.f;
+    }
 #pragma unroll
     for (int r = 0; r < kIlp; ++r) cadd(s, x[r]);
-    edges += kIlp;
-  }
-  for (; e < end; e += stride) {
-    const int u = ii[e];
-    cadd(s, u < nhot ? hot[u] : src[u]);
-    ++edges;
   }
 }
 
@@ -148,7 +150,7 @@ struct Track {
   CSum change;                  // L1 norm of x_{t+1} - x_t
   CSum arcs;                    // their out-arcs (what a push step would send)
 };
-SX_DEV void pr_finish_tracked(const PrArgs &a, int v, CSum s, float D, float *dst, CSum &dang,
+SX_DEV void pr_finish_tracked(const PrArgs &a, int v, int od, CSum s, float D, float *dst, CSum &dang,
                               Track &tr) {
   const float d = a.P.pr_d;
   const float r = a.base_teleport + d * ((s.s + s.c) + D * a.inv_n);
@@ -157,7 +159,6 @@ SX_DEV void pr_finish_tracked(const PrArgs &a, int v, CSum s, float D, float *ds
   const float pend = (r - r0) - tr.cu;
   a.w.prd[v] = pend;
   cadd(tr.change, fabsf(r - r0));
-  const int od = a.g.off[v + 1] - a.g.off[v];
   if (fabsf(pend) > a.thr) {
     tr.active += 1.f;
     cadd(tr.arcs, (float)od);
@@ -167,104 +168,96 @@ SX_DEV void pr_finish_tracked(const PrArgs &a, int v, CSum s, float D, float *ds
 }
 
 template <bool kTrack>
-SX_DEV void pr_iteration(const PrArgs &a, int t, const ViewRef &L, const Totals &T, LdsPr &lds,
-                         float D, Track &tr, float *hot) {
+SX_DEV void pr_iteration(const PrArgs &a, int t, const Rows &rows, LdsPull &lds, float D, Track &tr, float *hot) {
   const Work &w = a.w;
   const float *src = w.contrib[t & 1];
   const int nhot = a.g.n < kHotPr ? a.g.n : kHotPr;
   stage_hot(hot, src, nhot);
   float *dst = w.contrib[(t + 1) & 1];
   const bool last = !kTrack && t == a.iters - 1;
-  auto finish = [&](int v, CSum s, CSum &dang) {
-    if constexpr (kTrack) pr_finish_tracked(a, v, s, D, dst, dang, tr);
-    else pr_finish_vertex(a, v, s, D, last, dst, dang);
-  };
-  const int *io = a.g.in_off, *ii = a.g.in_idx;
-  const int lane = lane_id();
   CSum dang{0.f, 0.f};
-  long long edges = 0;
-  // one workgroup per large vertex
-  for (unsigned i = blockIdx.x; i < T.cnt[BIN_LARGE]; i += gridDim.x) {
-    const int v = (int)(L.large(i) & 0xffffffffu);
-    if ((unsigned)v >= (unsigned)a.g.n) continue;
-    const int beg = io[v], end = io[v + 1];
+  auto finish = [&](const Row &x, CSum s) {
+    if constexpr (kTrack) pr_finish_tracked(a, x.v, x.od, s, D, dst, dang, tr);
+    else pr_finish_vertex(a, x.v, x.od, s, D, last, dst, dang);
+  };
+  const int *ii = a.g.in_idx;
+  // one workgroup per long row
+  for (unsigned i = rows.at[5] + blockIdx.x; i < rows.at[6]; i += gridDim.x) {
+    const Row x = row_load(rows, i, rows.at[6]);
     CSum s{0.f, 0.f};
-    gather(s, src, ii, beg + (int)threadIdx.x, end, kBlock, edges, hot, nhot);
-    s = wg_merge(s, lds.f);
-    if (threadIdx.x == 0) finish(v, s, dang);
+    gather(s, src, ii, x.beg, (int)threadIdx.x, x.len, kPullBlock, hot, nhot);
+    s = pull_merge1(s, lds.f);
+    if (threadIdx.x == 0) finish(x, s);
   }
-  const unsigned gw = blockIdx.x * kWaves + wave_in_wg();
-  const unsigned nw = gridDim.x * kWaves;
-  // one wavefront per medium vertex
-  for (unsigned i = gw; i < T.cnt[BIN_MED]; i += nw) {
-    const int v = L.med(i);
-    if ((unsigned)v >= (unsigned)a.g.n) continue;
-    const int beg = io[v], end = io[v + 1];
-    CSum s{0.f, 0.f};
-    gather(s, src, ii, beg + lane, end, 64, edges, hot, nhot);
-    s = wave_merge(s);
-    if (lane == 0) finish(v, s, dang);
-  }
-  // one lane per small vertex
-  for (unsigned i = gw * 64u + lane; i < T.cnt[BIN_SMALL]; i += nw * 64u) {
-    const int v = L.small(i);
-    if ((unsigned)v >= (unsigned)a.g.n) continue;
-    const int beg = io[v], end = io[v + 1];
-    CSum s{0.f, 0.f};
-    gather(s, src, ii, beg, end, 1, edges, hot, nhot);
-    finish(v, s, dang);
-  }
-  dang = wg_merge(dang, lds.f);
-  if (threadIdx.x == 0) {
-    float *part = w.dang + (size_t)((t + 1) & 1) * 2 * kMaxGrid;
-    part[2 * blockIdx.x] = dang.s;
-    part[2 * blockIdx.x + 1] = dang.c;
-  }
+  const unsigned gw = blockIdx.x * kPullWaves + wave_in_wg();
+  const unsigned nw = gridDim.x * kPullWaves;
+  unsigned turn = 0;
+  auto some = [&](auto lanes, int cls) {
+    constexpr int kLanes = decltype(lanes)::value;
+    rows_walk<kLanes>(rows, cls, gw, nw, turn, [&](const Row &x, int sub) {
+      CSum s{0.f, 0.f};
+      gather(s, src, ii, x.beg, sub, x.len, kLanes, hot, nhot);
+      s = lanes_merge<kLanes>(s);
+      if (sub == 0 && x.v >= 0) finish(x, s);
+    });
+  };
+  some(std::integral_constant<int, 64>(), 4);
+  some(std::integral_constant<int, 16>(), 3);
+  some(std::integral_constant<int, 4>(), 2);
+  some(std::integral_constant<int, 1>(), 1);
+  rows_walk<1>(rows, 0, gw, nw, turn, [&](const Row &x, int) {
+    if (x.v >= 0) finish(x, CSum{0.f, 0.f});
+  });
+  // this workgroup's partial sums
+  float *part = w.dang + (size_t)((t + 1) & 1) * 2 * kMaxGrid;
   if constexpr (kTrack) {
-    const CSum ch = wg_merge(tr.change, lds.f);
-    const CSum ac = wg_merge(CSum{tr.active, 0.f}, lds.f);
-    const CSum ar = wg_merge(tr.arcs, lds.f);
+    CSum p[4] = {dang, tr.change, tr.arcs, CSum{tr.active, 0.f}};
+    pull_merge(p, lds.f);
     if (threadIdx.x == 0) {
+      part[2 * blockIdx.x] = p[0].s;
+      part[2 * blockIdx.x + 1] = p[0].c;
       float *q = w.prp + ((size_t)(t & 1) * kMaxGrid + blockIdx.x) * 8;
-      q[0] = ac.s + ac.c;
-      q[1] = ch.s;
-      q[2] = ch.c;
-      q[3] = ar.s;
-      q[4] = ar.c;
+      q[0] = p[3].s + p[3].c;
+      q[1] = p[1].s;
+      q[2] = p[1].c;
+      q[3] = p[2].s;
+      q[4] = p[2].c;
+    }
+  } else {
+    dang = pull_merge1(dang, lds.f);
+    if (threadIdx.x == 0) {
+      part[2 * blockIdx.x] = dang.s;
+      part[2 * blockIdx.x + 1] = dang.c;
     }
   }
-  add_stats(w.ctrl, blockIdx.x, edges, 0ull, lds.red);
 }
 
-__global__ void __launch_bounds__(kBlock) k_pr_fused(PrArgs a) {
-  __shared__ LdsPr lds;
+// Statistics of `iters` pull iterations, all arcs and vertices each (one
+// thread).
+SX_DEV void pr_pull_stats(const PrArgs &a, int iters) {
+  atomic_add_u64((unsigned long long *)&a.w.ctrl->statw[0].v[0], (unsigned long long)iters * (unsigned long long)a.g.m);
+}
+
+__global__ void __launch_bounds__(kPullBlock) k_pr_fused(PrArgs a) {
+  __shared__ LdsPull lds;
   __shared__ float hot[kHotPr];
   Ctrl *C = a.w.ctrl;
   const VGrid vg = hw_grid();
   GridBarrier bar(C, load_relaxed(&C->bar_gen.v[0]), a.P.watchdog);
-  pr_lists(a, lds);
-  if (!bar.sync()) return;
-  ViewRef L;
-  L.V = &lds.view;
-  L.R = regions(a.w, 0, vg.nb);
-  L.G = vg.nb;
-  const Totals T = view_build(a.w.rec + SLOT_SCAN, vg.nb, L.R, lds.view, lds.red);
-  if (T.ovf) {
-    if (threadIdx.x == 0) store_relaxed(&C->error.v[0], (unsigned)SX_ERR_CAPACITY);
-    return;
-  }
+  Rows rows;
+  if (!pr_rows(a, vg, bar, lds, rows)) return;
   for (int t = 0; t < a.iters; ++t) {
     const float D = dangling_total(a.w.dang + (size_t)(t & 1) * 2 * kMaxGrid, gridDim.x, lds.f);
-    Track none{0.f, 0.f, CSum{0.f, 0.f}};
-    pr_iteration<false>(a, t, L, T, lds, D, none, hot);
+    Track none{0.f, 0.f, CSum{0.f, 0.f}, CSum{0.f, 0.f}};
+    pr_iteration<false>(a, t, rows, lds, D, none, hot);
     if (!bar.sync()) return;
   }
   if (vg.bid == 0 && threadIdx.x == 0) {
     store_relaxed(&C->state.v[0], (unsigned)EXIT_DONE);
     store_relaxed(&C->stats.v[6], (unsigned)a.iters);
     store_relaxed(&C->stats.v[4], 1u);
-    atomic_add_u64((unsigned long long *)&C->statw[0].v[2],
-                   (unsigned long long)a.iters * ((unsigned long long)T.cnt[0] + T.cnt[1] + T.cnt[2]));
+    pr_pull_stats(a, a.iters);
+    atomic_add_u64((unsigned long long *)&C->statw[0].v[2], (unsigned long long)a.iters * (unsigned long long)a.g.n);
   }
 }
 
@@ -376,34 +369,34 @@ SX_DEV void pr_push_ballot(const PrArgs &a, int p, LdsPr &lds) {
   if (blockIdx.x == 0 && threadIdx.x == 0) atomic_add_u32(&a.w.ctrl->stats.v[4], 1u);
 }
 
-// Sum of a per-workgroup value at q[(par * kMaxGrid + b) * 8 + k] over the
-// grid, fixed order (identical in every workgroup).
-SX_DEV CSum partial_sum(const float *prp, int par, int k, int kc, float *lf) {
-  CSum acc{0.f, 0.f};
-  for (unsigned b = threadIdx.x; b < gridDim.x; b += kBlock) {
-    const float *q = prp + ((size_t)par * kMaxGrid + b) * 8;
-    acc = cmerge(acc, CSum{q[k], kc >= 0 ? q[kc] : 0.f});
-  }
-  return wg_merge(acc, lf);
+// Sum over a workgroup of kThreads threads.
+template <int kThreads>
+SX_DEV CSum any_merge(CSum a, float *lf) {
+  if constexpr (kThreads == kPullBlock) return pull_merge1(a, lf);
+  else return wg_merge(a, lf);
 }
 
 // Normalisation to sum 1 (every workgroup of the grid; a global barrier
 // between the partial sums and the division); false if the barrier failed.
-SX_DEV bool pr_normalize(const PrArgs &a, const VGrid &vg, GridBarrier &bar, LdsPr &lds) {
+template <int kThreads>
+SX_DEV bool pr_normalize(const PrArgs &a, const VGrid &vg, GridBarrier &bar, float *lf) {
   const int n = a.g.n;
   CSum sum{0.f, 0.f};
-  for (long long v = (long long)vg.bid * kBlock + threadIdx.x; v < n; v += (long long)vg.nb * kBlock)
+  for (long long v = (long long)vg.bid * kThreads + threadIdx.x; v < n; v += (long long)vg.nb * kThreads)
     cadd(sum, a.rank[v]);
-  sum = wg_merge(sum, lds.f);
+  sum = any_merge<kThreads>(sum, lf);
   if (threadIdx.x == 0) {
-    float *q = a.w.prp + ((size_t)0 * kMaxGrid + vg.bid) * 8;
+    float *q = a.w.prp + (size_t)vg.bid * 8;
     q[6] = sum.s;
     q[7] = sum.c;
   }
   if (!bar.sync()) return false;
-  const CSum tot = partial_sum(a.w.prp, 0, 6, 7, lds.f);
+  CSum tot{0.f, 0.f};
+  for (unsigned b = threadIdx.x; b < vg.nb; b += kThreads)
+    tot = cmerge(tot, CSum{a.w.prp[(size_t)b * 8 + 6], a.w.prp[(size_t)b * 8 + 7]});
+  tot = any_merge<kThreads>(tot, lf);
   const float S1 = tot.s + tot.c;
-  for (long long v = (long long)vg.bid * kBlock + threadIdx.x; v < n; v += (long long)vg.nb * kBlock)
+  for (long long v = (long long)vg.bid * kThreads + threadIdx.x; v < n; v += (long long)vg.nb * kThreads)
     a.rank[v] = a.rank[v] / S1;
   return true;
 }
@@ -429,47 +422,47 @@ enum { PRX_CU = 0, PRX_PULLS = 1, PRX_ENTRIES = 2 };
 // host launches the push kernel.  Each kernel runs at the occupancy of its
 // own registers (one kernel holding both ran the pull at one workgroup per
 // CU: 2.5 against 1.8 ms per iteration at s24).
-__global__ void __launch_bounds__(kBlock) k_pr_conv_pull(PrArgs a) {
-  __shared__ LdsPr lds;
+__global__ void __launch_bounds__(kPullBlock) k_pr_conv_pull(PrArgs a) {
+  __shared__ LdsPull lds;
   __shared__ float hot[kHotPr];
   Ctrl *C = a.w.ctrl;
   const VGrid vg = hw_grid();
   GridBarrier bar(C, load_relaxed(&C->bar_gen.v[0]), a.P.watchdog);
   const int n = a.g.n;
-  pr_lists(a, lds);
-  if (!bar.sync()) return;
-  ViewRef L;
-  L.V = &lds.view;
-  L.R = regions(a.w, 0, vg.nb);
-  L.G = vg.nb;
-  const Totals T = view_build(a.w.rec + SLOT_SCAN, vg.nb, L.R, lds.view, lds.red);
-  if (T.ovf) {
-    if (threadIdx.x == 0) store_relaxed(&C->error.v[0], (unsigned)SX_ERR_CAPACITY);
-    return;
-  }
-  float Dprev = 0.f, cu = 0.f;
+  Rows rows;
+  if (!pr_rows(a, vg, bar, lds, rows)) return;
+  float D = dangling_total(a.w.dang, gridDim.x, lds.f), Dprev = 0.f, cu = 0.f;
   int t = 0;
   bool tail = false;
   for (;; ++t) {
-    const float D = dangling_total(a.w.dang + (size_t)(t & 1) * 2 * kMaxGrid, gridDim.x, lds.f);
     cu = t == 0 ? 0.f : a.P.pr_d * (D - Dprev) * a.inv_n;
     Dprev = D;
     Track tr{cu, 0.f, CSum{0.f, 0.f}, CSum{0.f, 0.f}};
-    pr_iteration<true>(a, t, L, T, lds, D, tr, hot);
+    pr_iteration<true>(a, t, rows, lds, D, tr, hot);
     if (!bar.sync()) return;
-    // the decision tree, evaluated identically by every workgroup
-    const CSum ch = partial_sum(a.w.prp, t & 1, 1, 2, lds.f);
-    const CSum ac = partial_sum(a.w.prp, t & 1, 0, -1, lds.f);
-    const CSum ar = partial_sum(a.w.prp, t & 1, 3, 4, lds.f);
-    if (ch.s + ch.c <= a.stop_change) break;
-    if ((t >= 1 && ac.s + ac.c <= 0.5f * (float)n && (ar.s + ar.c) * kPushArcCost <= (float)a.g.m) ||
+    // the decision tree, evaluated identically by every workgroup; with it the
+    // dangling mass of the next iteration
+    CSum p[4] = {CSum{0.f, 0.f}, CSum{0.f, 0.f}, CSum{0.f, 0.f}, CSum{0.f, 0.f}};
+    const float *part = a.w.dang + (size_t)((t + 1) & 1) * 2 * kMaxGrid;
+    for (unsigned b = threadIdx.x; b < gridDim.x; b += kPullBlock) {
+      const float *q = a.w.prp + ((size_t)(t & 1) * kMaxGrid + b) * 8;
+      p[0] = cmerge(p[0], CSum{q[1], q[2]});
+      p[1] = cmerge(p[1], CSum{q[0], 0.f});
+      p[2] = cmerge(p[2], CSum{q[3], q[4]});
+      p[3] = cmerge(p[3], CSum{part[2 * b], part[2 * b + 1]});
+    }
+    pull_merge(p, lds.f);
+    D = p[3].s + p[3].c;
+    if (p[0].s + p[0].c <= a.stop_change) break;
+    if ((t >= 1 && p[1].s + p[1].c <= 0.5f * (float)n && (p[2].s + p[2].c) * kPushArcCost <= (float)a.g.m) ||
         t + 1 >= a.max_pull) {
       tail = true;
       break;
     }
   }
   const int pulls = t + 1;
-  const unsigned long long entries = (unsigned long long)pulls * ((unsigned long long)T.cnt[0] + T.cnt[1] + T.cnt[2]);
+  const unsigned long long entries = (unsigned long long)pulls * (unsigned long long)n;
+  if (vg.bid == 0 && threadIdx.x == 0) pr_pull_stats(a, pulls);
   if (tail) {
     if (vg.bid == 0 && threadIdx.x == 0) {
       store_relaxed(&C->aux.v[PRX_CU], __float_as_uint(cu));
@@ -479,7 +472,7 @@ __global__ void __launch_bounds__(kBlock) k_pr_conv_pull(PrArgs a) {
     }
     return;
   }
-  if (!pr_normalize(a, vg, bar, lds)) return;
+  if (!pr_normalize<kPullBlock>(a, vg, bar, lds.f)) return;
   if (vg.bid == 0 && threadIdx.x == 0) pr_conv_done(C, pulls, 0, entries);
 }
 
@@ -531,24 +524,24 @@ __global__ void __launch_bounds__(kBlock) k_pr_conv_push(PrArgs a) {
     if (!bar.sync()) return;
     slot = (j + 1) % 3;
   }
-  if (!pr_normalize(a, vg, bar, lds)) return;
+  if (!pr_normalize<kBlock>(a, vg, bar, lds.f)) return;
   if (vg.bid == 0 && threadIdx.x == 0) pr_conv_done(C, pulls, steps, entries);
 }
 
 // x_0 = 1/n: contributions and the dangling partials of iteration 0 (same
 // grid as the persistent kernel, so partial i belongs to workgroup i).
-__global__ void __launch_bounds__(kBlock) k_pr_init(PrArgs a) {
-  __shared__ float lf[2 * kWaves];
+__global__ void __launch_bounds__(kPullBlock) k_pr_init(PrArgs a) {
+  __shared__ float lf[2 * kPullWaves];
   const int n = a.g.n;
   CSum dang{0.f, 0.f};
-  for (long long v = (long long)blockIdx.x * kBlock + threadIdx.x; v < n;
-       v += (long long)gridDim.x * kBlock) {
+  for (long long v = (long long)blockIdx.x * kPullBlock + threadIdx.x; v < n;
+       v += (long long)gridDim.x * kPullBlock) {
     const int od = a.g.off[v + 1] - a.g.off[v];
     if (od > 0) a.w.contrib[0][v] = a.inv_n / (float)od;
     else cadd(dang, a.inv_n);
     if (a.conv) a.rank[v] = a.inv_n;
   }
-  dang = wg_merge(dang, lf);
+  dang = pull_merge1(dang, lf);
   if (threadIdx.x == 0) {
     a.w.dang[2 * blockIdx.x] = dang.s;
     a.w.dang[2 * blockIdx.x + 1] = dang.c;
@@ -564,9 +557,9 @@ __global__ void __launch_bounds__(kBlock) k_pr_init(PrArgs a) {
 }
 
 hipError_t pagerank_launch(const PrArgs &a, int grid, hipStream_t s) {
-  hipLaunchKernelGGL(k_pr_init, dim3(grid), dim3(kBlock), 0, s, a);
-  if (a.conv) hipLaunchKernelGGL(k_pr_conv_pull, dim3(grid), dim3(kBlock), 0, s, a);
-  else hipLaunchKernelGGL(k_pr_fused, dim3(grid), dim3(kBlock), 0, s, a);
+  hipLaunchKernelGGL(k_pr_init, dim3(grid), dim3(kPullBlock), 0, s, a);
+  if (a.conv) hipLaunchKernelGGL(k_pr_conv_pull, dim3(grid), dim3(kPullBlock), 0, s, a);
+  else hipLaunchKernelGGL(k_pr_fused, dim3(grid), dim3(kPullBlock), 0, s, a);
   return hipGetLastError();
 }
 
@@ -575,6 +568,7 @@ hipError_t pagerank_push_launch(const PrArgs &a, int grid, hipStream_t s) {
   return hipGetLastError();
 }
 
+static_assert(kPagerankBlock == kPullBlock, "host and kernel agree on the workgroup");
 const void *pagerank_kernel(bool conv) { return conv ? (const void *)k_pr_conv_pull : (const void *)k_pr_fused; }
 const void *pagerank_push_kernel() { return (const void *)k_pr_conv_push; }
 
