@@ -145,7 +145,9 @@ sx_status sx_graph_info(const sx_graph *g, int32_t *n, int64_t *m, int32_t *dire
  *              from b = phi.  d_out holds the priors p_v (float, each in
  *              (0, 1), else SX_EINVAL) on entry and the beliefs b(v, 1) on
  *              return (FP32 arithmetic, compensated sums).  Undirected
- *              graphs only (SX_EUNSUPPORTED otherwise); pass source -1. */
+ *              graphs only (SX_EUNSUPPORTED otherwise); pass source -1.
+ *              The first run of several iterations on a graph adds 4 bytes
+ *              an arc to its workspace, if the device has them. */
 typedef enum { SX_BFS = 0, SX_SSSP = 1, SX_KCORE = 2, SX_PAGERANK = 3, SX_WCC = 4, SX_BP = 5 } sx_algo;
 
 /* sssp_delta: bucket width of delta-stepping for SX_SSSP (Section 3.3: the

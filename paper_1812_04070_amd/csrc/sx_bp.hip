@@ -15,27 +15,22 @@
 // and the belief is b_v = 1 / (1 + exp(-2 x_v)).
 //
 //   Active   every vertex, every iteration.
-//   Compute  atanh(c_uv q_u) from the neighbour's (q_u, deg u), stored per
-//            vertex once per iteration (one 8-byte gather per arc) and the
-//            arc's weight (read with the neighbour id, coalesced).
+//   Compute  atanh(c_uv q_u) from the neighbour's q_u, stored per vertex once
+//            per iteration, and the arc's coupling (the first iteration's
+//            gathers bring the neighbour's degree too).
 //   Combine  sum over the neighbours (aggregation), single writer per
 //            vertex, compensated FP32 in a fixed order.
 //
-// Task management as for PageRank: the binned vertex lists come from one
-// ballot-filter pass before the first iteration (Section 4: BP needs the
-// ballot filter exactly once) and are reused; one persistent launch runs all
-// iterations, with one global barrier each (Section 5).
-#include "sx_frontier.hpp"
+// Task management as for PageRank: every vertex's row, classed by length once
+// before the first iteration (Section 4: BP needs the ballot filter exactly
+// once) and reused; one persistent launch runs all iterations, with one global
+// barrier each (Section 5).
+#include <type_traits>
+
 #include "sx_kernels.hpp"
+#include "sx_rows.hpp"
 
 namespace sx {
-
-struct LdsBp {
-  LdsView view;
-  LdsBallot ball;
-  long long red[kWaves];
-  float f[2 * kWaves];
-};
 
 // Coupling sign and strength of an arc from its weight (weights 1..64 span
 // -1..1; an unweighted graph couples every edge with theta = 1).
@@ -43,132 +38,135 @@ SX_DEV float bp_theta(const unsigned *w, long long e) {
   return w ? ((float)((w[e] - 1u) & 63u) - 31.5f) / 31.5f : 1.f;
 }
 
-// (q, deg) of the first kHotBp vertices, copied into LDS by every workgroup
-// at the start of each iteration: after the degree-ordered renumbering they
-// are the highest-degree neighbours, and a gather served by LDS is one
-// request fewer at the L2 (the pull's bound, as for PageRank).
-constexpr int kHotBp = 4096;
+// atanh: the odd series up to x^7 for |x| <= 1/16, where the next term is
+// below 3e-11 of x and the leading x carries the only rounding that counts
+// (the couplings of all but low-degree pairs); the library's function beyond.
+SX_DEV float bp_atanh(float x) {
+  const float x2 = x * x;
+  const float t = x2 * fmaf(x2, fmaf(x2, 1.f / 7.f, 0.2f), 1.f / 3.f);
+  return fabsf(x) <= 0.0625f ? fmaf(x, t, x) : atanhf(x);
+}
 
-// s += atanh(c_uv q_u) over the arcs e = e0, e0 + stride, ... < end of
-// vertex v (degree dv), kIlp arcs in flight per lane, added in order (an
-// index below nhot reads the LDS copy hot).
-SX_DEV void bp_gather(CSum &s, const BpArgs &a, const float2 *src, float dv, long long e0, long long end,
-                      int stride, long long &edges, const float2 *hot, int nhot) {
+// The hottest neighbours' state in LDS, as for PageRank (sx_pagerank.hip):
+// q alone, or (q, deg) pairs for half as many.
+constexpr int kHotBp = 39936;
+
+// How an iteration gets an arc's coupling c_uv = kappa theta / max(deg, deg):
+// from the weight and the gathered degree (kBpWeigh); the same, and stores it
+// (kBpStore: the first of several iterations); or from the store (kBpStored),
+// so that the others gather 4 bytes an arc and divide nothing.
+enum { kBpWeigh, kBpStore, kBpStored };
+
+// s += atanh(c_uv q_u) over the arcs beg + e, e = e0, e0 + stride, ... < len of
+// a vertex of degree len, kIlp arcs of a lane in flight, added in order.
+// Whole wavefronts; a place past the row's end adds zero (as in sx_pagerank.hip).
+template <int kMode>
+SX_DEV void bp_gather(CSum &s, const BpArgs &a, const float2 *src2, const float *src, int beg, int e0, int len,
+                      int stride, const float *hot, int nhot) {
   const int *ii = a.g.idx;
-  const unsigned *ww = a.g.w;
-  long long e = e0;
-  for (; e + (long long)(kIlp - 1) * stride < end; e += (long long)kIlp * stride) {
+  const float dv = (float)len;
+  for (int e = e0; ballot(e < len); e += kIlp * stride) {
     int u[kIlp];
-    float th[kIlp];
-    float2 su[kIlp];
+    float c[kIlp], q[kIlp];
 #pragma unroll
     for (int r = 0; r < kIlp; ++r) {
-      u[r] = ii[e + r * stride];
-      th[r] = bp_theta(ww, e + r * stride);
+      const int at = beg + (e + r * stride < len ? e + r * stride : 0);
+      u[r] = ii[at];
+      c[r] = kMode == kBpStored ? a.couple[at] : bp_theta(a.g.w, at);
     }
 #pragma unroll
-    for (int r = 0; r < kIlp; ++r) su[r] = u[r] < nhot ? hot[u[r]] : src[u[r]];
+    for (int r = 0; r < kIlp; ++r) {
+      const bool ok = e + r * stride < len;
+      const int i = ok ? u[r] : 0;
+      if constexpr (kMode == kBpStored) {
+        q[r] = i < nhot ? hot[i] : src[i];
+      } else {
+        const float2 x = i < nhot ? ((const float2 *)hot)[i] : src2[i];
+        q[r] = x.x;
+        c[r] = a.kappa * c[r] / fmaxf(x.y, dv);
+        if (kMode == kBpStore && ok) a.couple[beg + e + r * stride] = c[r];
+      }
+      q[r] = ok ? c[r] * q[r] : 0.f;
+    }
 #pragma unroll
-    for (int r = 0; r < kIlp; ++r) cadd(s, atanhf(a.kappa * th[r] / fmaxf(su[r].y, dv) * su[r].x));
-    edges += kIlp;
-  }
-  for (; e < end; e += stride) {
-    const int uu = ii[e];
-    const float2 su = uu < nhot ? hot[uu] : src[uu];
-    cadd(s, atanhf(a.kappa * bp_theta(ww, e) / fmaxf(su.y, dv) * su.x));
-    ++edges;
+    for (int r = 0; r < kIlp; ++r) cadd(s, bp_atanh(q[r]));
   }
 }
 
-// One vertex's new state from its neighbour sum: (q, deg) for the next
-// iteration, or the belief after the last one.
-SX_DEV void bp_finish_vertex(const BpArgs &a, int v, CSum s, float dv, bool last, float2 *dst) {
-  const float x = a.w.bph[v] + (s.s + s.c);
-  if (last) a.belief[v] = 1.f / (1.f + expf(-2.f * x));
-  else dst[v] = make_float2(tanhf(x), dv);
-}
-
-SX_DEV void bp_iteration(const BpArgs &a, int t, const ViewRef &L, const Totals &T, LdsBp &lds,
-                         float2 *hot) {
-  const float2 *src = a.w.bpq[t & 1];
-  const int nhot = a.g.n < kHotBp ? a.g.n : kHotBp;
-  for (int i = threadIdx.x; i < nhot; i += kBlock) hot[i] = src[i];
+// One iteration; `last` writes beliefs, else the next state (q alone from a
+// run that stores its couplings, else (q, deg)).
+template <int kMode>
+SX_DEV void bp_iteration(const BpArgs &a, int t, const Rows &rows, float *lf, float *hot) {
+  const float2 *src2 = a.w.bpq[t & 1];
+  const float *src = a.w.contrib[t & 1];
+  constexpr int words = kMode == kBpStored ? 1 : 2, most = kHotBp / words;
+  const int nhot = a.g.n < most ? a.g.n : most;
+  const float *from = kMode == kBpStored ? src : (const float *)src2;
+  for (int i = threadIdx.x; i < nhot * words; i += kPullBlock) hot[i] = from[i];
   __syncthreads();
-  float2 *dst = a.w.bpq[(t + 1) & 1];
   const bool last = t == a.iters - 1;
-  const int *off = a.g.off;
-  const int lane = lane_id();
-  long long edges = 0;
-  // one workgroup per large vertex
-  for (unsigned i = blockIdx.x; i < T.cnt[BIN_LARGE]; i += gridDim.x) {
-    const int v = (int)(L.large(i) & 0xffffffffu);
-    if ((unsigned)v >= (unsigned)a.g.n) continue;
-    const long long beg = off[v], end = off[v + 1];
-    const float dv = (float)(end - beg);
+  auto finish = [&](const Row &x, CSum s) {
+    const float f = a.w.bph[x.v] + (s.s + s.c);
+    if (last) a.belief[x.v] = 1.f / (1.f + expf(-2.f * f));
+    else if (kMode == kBpWeigh) a.w.bpq[(t + 1) & 1][x.v] = make_float2(tanhf(f), (float)x.len);
+    else a.w.contrib[(t + 1) & 1][x.v] = tanhf(f);
+  };
+  // one workgroup per long row
+  for (unsigned i = rows.at[5] + blockIdx.x; i < rows.at[6]; i += gridDim.x) {
+    const Row x = row_load(rows, i, rows.at[6]);
     CSum s{0.f, 0.f};
-    bp_gather(s, a, src, dv, beg + threadIdx.x, end, kBlock, edges, hot, nhot);
-    s = wg_merge(s, lds.f);
-    if (threadIdx.x == 0) bp_finish_vertex(a, v, s, dv, last, dst);
+    bp_gather<kMode>(s, a, src2, src, x.beg, (int)threadIdx.x, x.len, kPullBlock, hot, nhot);
+    s = pull_merge1(s, lf);
+    if (threadIdx.x == 0) finish(x, s);
   }
-  const unsigned gw = blockIdx.x * kWaves + wave_in_wg();
-  const unsigned nw = gridDim.x * kWaves;
-  // one wavefront per medium vertex
-  for (unsigned i = gw; i < T.cnt[BIN_MED]; i += nw) {
-    const int v = L.med(i);
-    if ((unsigned)v >= (unsigned)a.g.n) continue;
-    const long long beg = off[v], end = off[v + 1];
-    const float dv = (float)(end - beg);
-    CSum s{0.f, 0.f};
-    bp_gather(s, a, src, dv, beg + lane, end, 64, edges, hot, nhot);
-    s = wave_merge(s);
-    if (lane == 0) bp_finish_vertex(a, v, s, dv, last, dst);
-  }
-  // one lane per small vertex
-  for (unsigned i = gw * 64u + lane; i < T.cnt[BIN_SMALL]; i += nw * 64u) {
-    const int v = L.small(i);
-    if ((unsigned)v >= (unsigned)a.g.n) continue;
-    const long long beg = off[v], end = off[v + 1];
-    const float dv = (float)(end - beg);
-    CSum s{0.f, 0.f};
-    bp_gather(s, a, src, dv, beg, end, 1, edges, hot, nhot);
-    bp_finish_vertex(a, v, s, dv, last, dst);
-  }
-  add_stats(a.w.ctrl, blockIdx.x, edges, 0ull, lds.red);
+  const unsigned gw = blockIdx.x * kPullWaves + wave_in_wg();
+  const unsigned nw = gridDim.x * kPullWaves;
+  unsigned turn = 0;
+  auto some = [&](auto lanes, int cls) {
+    constexpr int kLanes = decltype(lanes)::value;
+    rows_walk<kLanes>(rows, cls, gw, nw, turn, [&](const Row &x, int sub) {
+      CSum s{0.f, 0.f};
+      bp_gather<kMode>(s, a, src2, src, x.beg, sub, x.len, kLanes, hot, nhot);
+      s = lanes_merge<kLanes>(s);
+      if (sub == 0 && x.v >= 0) finish(x, s);
+    });
+  };
+  some(std::integral_constant<int, 64>(), 4);
+  some(std::integral_constant<int, 16>(), 3);
+  some(std::integral_constant<int, 4>(), 2);
+  some(std::integral_constant<int, 1>(), 1);
+  rows_walk<1>(rows, 0, gw, nw, turn, [&](const Row &x, int) {
+    if (x.v >= 0) finish(x, CSum{0.f, 0.f});
+  });
 }
 
-__global__ void __launch_bounds__(kBlock) k_bp_fused(BpArgs a) {
-  __shared__ LdsBp lds;
-  __shared__ float2 hot[kHotBp];
+// Bounds: the gathers, as for PageRank, and the arithmetic of an arc: with two
+// divisions and the library's atanh it took 12.5 ms for 10 iterations of R-MAT
+// s22; with the couplings stored by the first iteration, the short series and
+// the row classes 7.5 (s20 3.75 -> 1.82, s16 1.03 -> 0.41).
+__global__ void __launch_bounds__(kPullBlock) k_bp_fused(BpArgs a) {
+  __shared__ LdsRows lds;
+  __shared__ float lf[2 * kPullWaves];
+  __shared__ alignas(8) float hot[kHotBp];
   Ctrl *C = a.w.ctrl;
   const VGrid vg = hw_grid();
   GridBarrier bar(C, load_relaxed(&C->bar_gen.v[0]), a.P.watchdog);
-  // every vertex, binned by degree: one ballot-filter pass
-  const int *off = a.g.off;
-  auto pred = [](int v) { (void)v; return true; };
-  auto deg = [&](int v) { return off[v + 1] - off[v]; };
-  auto ident = [](int i) { return i; };
-  ballot_fill(vg, a.g.n, pred, deg, ident, a.P, 0x7fffffff, a.w.bits, regions(a.w, 0, vg.nb),
-              a.w.rec + SLOT_SCAN, lds.ball);
+  rows_count(vg, a.w, a.g.n, a.g.off, a.P, lds);
   if (!bar.sync()) return;
-  ViewRef L;
-  L.V = &lds.view;
-  L.R = regions(a.w, 0, vg.nb);
-  L.G = vg.nb;
-  const Totals T = view_build(a.w.rec + SLOT_SCAN, vg.nb, L.R, lds.view, lds.red);
-  if (T.ovf) {
-    if (threadIdx.x == 0) store_relaxed(&C->error.v[0], (unsigned)SX_ERR_CAPACITY);
-    return;
-  }
+  const Rows rows = rows_place(vg, a.w, a.g.n, a.g.off, a.g.off, a.P, lds);
+  if (!bar.sync()) return;
   for (int t = 0; t < a.iters; ++t) {
-    bp_iteration(a, t, L, T, lds, hot);
+    if (!a.couple) bp_iteration<kBpWeigh>(a, t, rows, lf, hot);
+    else if (t == 0) bp_iteration<kBpStore>(a, t, rows, lf, hot);
+    else bp_iteration<kBpStored>(a, t, rows, lf, hot);
     if (!bar.sync()) return;
   }
   if (vg.bid == 0 && threadIdx.x == 0) {
     store_relaxed(&C->state.v[0], (unsigned)EXIT_DONE);
     store_relaxed(&C->stats.v[6], (unsigned)a.iters);
     store_relaxed(&C->stats.v[4], 1u);
-    atomic_add_u64((unsigned long long *)&C->statw[0].v[2],
-                   (unsigned long long)a.iters * ((unsigned long long)T.cnt[0] + T.cnt[1] + T.cnt[2]));
+    atomic_add_u64((unsigned long long *)&C->statw[0].v[0], (unsigned long long)a.iters * (unsigned long long)a.g.m);
+    atomic_add_u64((unsigned long long *)&C->statw[0].v[2], (unsigned long long)a.iters * (unsigned long long)a.g.n);
   }
 }
 
@@ -212,10 +210,11 @@ hipError_t bp_launch(const BpArgs &a, int grid, hipStream_t s) {
   hipLaunchKernelGGL(k_bp_clear_flag, dim3(1), dim3(64), 0, s, a.w.ctrl);
   hipLaunchKernelGGL(k_bp_init, dim3(grid), dim3(kBlock), 0, s, a);
   hipLaunchKernelGGL(k_bp_check, dim3(1), dim3(64), 0, s, a.w.ctrl);
-  hipLaunchKernelGGL(k_bp_fused, dim3(grid), dim3(kBlock), 0, s, a);
+  hipLaunchKernelGGL(k_bp_fused, dim3(grid), dim3(kPullBlock), 0, s, a);
   return hipGetLastError();
 }
 
+static_assert(kBpBlock == kPullBlock, "host and kernel agree on the workgroup");
 const void *bp_kernel() { return (const void *)k_bp_fused; }
 
 }  // namespace sx

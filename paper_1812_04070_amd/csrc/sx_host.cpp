@@ -115,6 +115,8 @@ struct sx_graph {
   std::vector<int> h_inv;
   unsigned *d_xdist = nullptr;  // SSSP / WCC expansion record (TravArgs::xdist)
   void *state = nullptr;
+  float *d_couple = nullptr;    // belief propagation: the arcs' couplings
+  bool no_couple = false;       // there was no memory for them
   long long weight_sum = -1;  // sum of the arc weights, once SX_DELTA_AUTO needed it
   // where the lists of the next iteration sit after sx_run_iterations:
   // record slot, region parity, run grid (-1: no such run yet)
@@ -1256,7 +1258,7 @@ static sx_status run_bp(sx_program *p, sx_graph *G, void *d_belief, hipStream_t 
     if (stats) memset(stats, 0, sizeof *stats);
     return SX_OK;
   }
-  const int grid = persistent_grid(p->ctx, bp_kernel(), p->pol.grid_wgs);
+  const int grid = persistent_grid(p->ctx, bp_kernel(), p->pol.grid_wgs, kBpBlock);
   BpArgs a;
   memset(&a, 0, sizeof a);
   a.g = G->g;
@@ -1267,6 +1269,20 @@ static sx_status run_bp(sx_program *p, sx_graph *G, void *d_belief, hipStream_t 
   a.belief = (float *)d_belief;
   a.kappa = p->ap.bp_kappa;
   a.iters = p->ap.bp_iters;
+  // several iterations share the arcs' couplings through an array the graph
+  // keeps from its first such run on (4 bytes an arc; the values are each
+  // run's own); where it cannot be had, every iteration weighs its arcs
+  if (a.iters > 1 && G->g.m > 0 && !G->d_couple && !G->no_couple) {
+    void *c = nullptr;
+    if (hipMalloc(&c, sizeof(float) * (size_t)G->g.m) == hipSuccess) {
+      G->owned.push_back(c);
+      G->d_couple = (float *)c;
+    } else {
+      (void)hipGetLastError();
+      G->no_couple = true;
+    }
+  }
+  a.couple = a.iters > 1 ? G->d_couple : nullptr;
   HIP_TRY(hipEventRecord(G->ev0, st));
   HIP_TRY(bp_launch(a, grid, st));
   HIP_TRY(hipEventRecord(G->ev1, st));
@@ -1897,7 +1913,7 @@ extern "C" sx_status sx_kernel_info_get(sx_ctx *ctx, const char *name, sx_kernel
       {"pagerank_fused", pagerank_kernel(), true, kPagerankBlock},
       {"pagerank_until_stable", pagerank_kernel(true), true, kPagerankBlock},
       {"pagerank_push_tail", pagerank_push_kernel(), true},
-      {"bp_fused", bp_kernel(), true},
+      {"bp_fused", bp_kernel(), true, kBpBlock},
       {"batch", batch_kernel(), true},
   };
   for (const Named &t : table) {

@@ -58,6 +58,7 @@ const void *pagerank_push_kernel();
 
 hipError_t bp_launch(const BpArgs &a, int grid, hipStream_t s);
 const void *bp_kernel();
+constexpr int kBpBlock = 1024;         // its threads per workgroup
 
 // Degree-ordered renumbering (graph loading option).  `own` allocates
 // device memory that the graph keeps, `tmp` memory freed after the build.

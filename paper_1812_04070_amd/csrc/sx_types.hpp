@@ -225,6 +225,8 @@ struct BpArgs {
   float *belief;                // in: prior P(x_v = 1); out: belief after iters
   float kappa;                  // coupling scale of the pairwise potentials
   int iters;
+  float *couple;                // [m] the arcs' couplings, written by the
+                                // first iteration; NULL: weighed every time
 };
 
 // Connected components by hooking (sx_wcc.hip).
