@@ -223,7 +223,9 @@ void sx_program_destroy(sx_program *p);
  *             graph of fewer than 8 arcs per vertex goes over to launches
  *             that each advance it by a window of distances once its
  *             frontier stays light: same results, and for BFS the same
- *             iteration count, the levels; so do a batch's queries)
+ *             iteration count, the levels; so do a batch's queries;
+ *             and a BFS, or an SSSP without buckets, of up to 24,576
+ *             vertices and few arcs is one launch of one workgroup)
  *  policy     SX_POLICY_HEURISTIC | SX_POLICY_LEARNED (MLP; needs
  *             sx_policy_load_mlp first)                                       */
 enum { SX_DIR_AUTO = 0, SX_DIR_PUSH = 1, SX_DIR_PULL = 2 };

@@ -1078,6 +1078,42 @@ static sx_status run_traversal(sx_program *p, sx_graph *G, int src, void *d_out,
   return SX_OK;
 }
 
+// ------------------------------------- small graphs in one workgroup ---
+// Whether a BFS / SSSP run takes sx_small.hip: the engine schedules it, it has
+// no buckets, and one workgroup is done with it before the grid's phases would
+// be.  us a run, phases -> one workgroup: BFS R-MAT s8 / s10 / s12 109 -> 37,
+// 117 -> 46, 116 -> 81, from 2^18 arcs on it loses (s14 137 -> 258); an SSSP
+// relaxes every arc two or three times, s10 192 -> 92, s12 (97 K arcs) 220 ->
+// 222 with the caller's numbering; grids, whose iterations are many and light,
+// as far as the LDS goes: side 155 (24,025 vertices) BFS 535 -> 343, SSSP
+// 4,470 -> 1,980.
+static bool small_run(const sx_program *p, const sx_graph *G) {
+  if (!engine_schedules(p->pol) || p->pol.policy != SX_POLICY_HEURISTIC || G->g.n > kSmallN) return false;
+  if (p->ap.algo == SX_BFS) return G->g.m <= (1ll << 17);
+  return p->ap.algo == SX_SSSP && (p->ap.sssp_delta == 0 || p->ap.sssp_delta == SX_DELTA_AUTO) &&
+         G->g.m <= std::max(1ll << 16, 4ll * G->g.n);
+}
+
+static sx_status run_small(sx_program *p, sx_graph *G, int src, void *d_out, hipStream_t st, sx_run_stats *stats) {
+  TravArgs a;
+  memset(&a, 0, sizeof a);
+  a.g = G->g;
+  a.w = G->w;
+  a.state_i = (int *)(G->reordered ? G->state : d_out);
+  a.src = src;
+  HIP_TRY(hipEventRecord(G->ev0, st));
+  HIP_TRY(small_launch(a, p->ap.algo == SX_SSSP, (int *)d_out, G->reordered ? G->d_inv : nullptr, st));
+  HIP_TRY(hipEventRecord(G->ev1, st));
+  sx_status s = read_ctrl(G, st);
+  if (s != SX_OK) return s;
+  s = ctrl_error(G->h_ctrl);
+  if (s != SX_OK) return s;
+  float ms = 0.f;
+  HIP_TRY(hipEventElapsedTime(&ms, G->ev0, G->ev1));
+  fill_stats(G->h_ctrl, 1, ms, 0, p->ctx->wall_khz, stats);
+  return SX_OK;
+}
+
 // ----------------------------------------- components by hooking ---
 // The paper's label propagation needs an iteration per hop and its frontier
 // machinery; hooking needs six or seven launches whatever the graph (us a run,
@@ -1680,6 +1716,7 @@ extern "C" sx_status sx_run(sx_program *p, const sx_graph *gc, int32_t source, v
       if (n == 0) return fail(SX_EINVAL, "empty graph has no source");
       if (source < 0 || source >= n) return fail(SX_EINVAL, "source %d out of range [0, %d)", source, n);
       if (p->ap.algo == SX_SSSP && !G->weighted) return fail(SX_EINVAL, "SSSP needs edge weights");
+      if (small_run(p, G)) return run_small(p, G, G->reordered ? G->h_inv[(size_t)source] : source, d_out, st, stats);
       s = run_traversal(p, G, G->reordered ? G->h_inv[(size_t)source] : source, state, st, stats);
       break;
     case SX_KCORE:
@@ -1806,6 +1843,7 @@ extern "C" sx_status sx_run_static(sx_program *p, const sx_graph_desc *d, int32_
   HIP_TRY(hipGetLastError());
   if (algo == SX_WCC && engine_schedules(p->pol) && p->pol.policy == SX_POLICY_HEURISTIC)
     return run_wcc(p, &G, d_out, st, stats);
+  if (small_run(p, &G)) return run_small(p, &G, source, d_out, st, stats);
   return run_traversal(p, &G, source, d_out, st, stats);
 }
 

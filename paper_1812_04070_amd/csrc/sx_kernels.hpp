@@ -23,6 +23,9 @@ hipError_t trav_launch(int kind, int algo, const TravArgs &a, int it, int arg, i
 // kernels); sequenced: also write the first state of a sequenced run
 hipError_t trav_init(const TravArgs &a, int algo, unsigned long long mu0, int run_grid,
                      hipStream_t s, bool pull_first = false, bool sequenced = false);
+// a whole BFS / SSSP of at most kSmallN vertices in one workgroup; out in the
+// caller's numbering (inv: renumbered graph)
+hipError_t small_launch(const TravArgs &a, bool weighted, int *out, const int *inv, hipStream_t s);
 hipError_t batch_launch(const BatchArgs &b, int grid, hipStream_t s);
 hipError_t weight_sum(const unsigned *w, long long m, unsigned long long *out, hipStream_t s);
 // phases of the sequenced mode (Ctrl::seq[..].v[0]); PH_CASCADE: launches of

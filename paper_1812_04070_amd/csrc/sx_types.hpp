@@ -15,6 +15,8 @@ constexpr int kTailThreads = 1024;       // and the workgroup's threads
 constexpr int kTailDefault = 16384;      // the tail's default hand-over: this
 constexpr unsigned long long kTailDefaultArcs = 1ull << 22;  // many vertices
                                          // and arcs at most
+constexpr int kSmallN = 24576;           // vertices whose distances one workgroup's
+                                         // LDS holds beside its lists (sx_small.hip)
 constexpr int kWaves = kBlock / 64;
 constexpr int kMaxGrid = 1024;           // upper bound on workgroups per grid
 // watchdog of the software global barrier: how long one wait may last, in
