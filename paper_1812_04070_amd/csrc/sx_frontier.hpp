@@ -335,9 +335,11 @@ struct ViewRef {
 // ------------------------------------------------------- ballot filter ---
 // Workgroup `bid` scans positions [lo, hi) (lo a multiple of 64); wavefront w
 // takes a contiguous sub-range, so the output order is the position order.
-// probe(pos, valid) is called convergently by whole wavefronts and returns
-// whether the entry at `pos` is active (false where !valid); vertex_of(pos)
-// and degree(v) give its vertex and degree.  The ballot words go to `bits`
+// look(pos, valid) reads the state of the entry at `pos`, want(state, valid)
+// says whether its degree matters, and keep(word, state, valid, wanted, degree),
+// called convergently by whole wavefronts for each tile (word: its ballot
+// word), whether it is active; vertex_of(pos) and degree(v) give its vertex
+// and degree.  The ballot words go to `bits`
 // (one 64-bit word per 64 positions per bin), are counted, and after a
 // workgroup barrier re-read and written into this workgroup's regions.  One
 // pass over the metadata and no grid-wide step: the range is contiguous, so
@@ -349,8 +351,10 @@ struct LdsBallot {
   unsigned long long wmf[kWaves];
 };
 
-template <class Probe, class Deg, class VertexOf>
-SX_DEV void ballot_fill_range(long long lo, long long hi, unsigned bid, Probe probe, Deg degree,
+constexpr int kScanIlp = 4;     // tiles of a wavefront in flight
+
+template <class Look, class Want, class Keep, class Deg, class VertexOf>
+SX_DEV void ballot_fill_range(long long lo, long long hi, unsigned bid, Look look, Want want, Keep keep, Deg degree,
                               VertexOf vertex_of, const Params &P, int chunk,
                               unsigned long long *const bits[NBINS], const Regions &R,
                               RecSlot *rec_slot, LdsBallot &lb) {
@@ -359,26 +363,46 @@ SX_DEV void ballot_fill_range(long long lo, long long hi, unsigned bid, Probe pr
   const int lane = lane_id(), wv = wave_in_wg();
   const long long start = lo + (long long)wv * per_wave;
   const long long end = start + per_wave < hi ? start + per_wave : hi;
+  // counts that need a sum over the lanes are kept per lane and summed once
+  // (a sum per tile was 18 of its cross-lane steps: with the frontier bitmap
+  // from the same pass, a BFS pull scan of R-MAT s22 40 -> 28 us)
   unsigned c[NBINS] = {0, 0, 0};
   unsigned long long mf = 0;
-  unsigned nfv = 0;
-  for (long long s = start; s < end; s += 64) {
-    const long long i = s + lane;
-    const bool p = probe(i, i < end);
-    const int d = p ? degree(vertex_of(i)) : 0;
-    const int b = p ? bin_of(d, P) : -1;
-    const long long word = s >> 6;
+  unsigned nfv = 0, large = 0;
+  for (long long s0 = start; s0 < end; s0 += 64 * kScanIlp) {
+    // the tiles' states, then their degrees, each in flight together
+    decltype(look(start, true)) x[kScanIlp];
+    bool p[kScanIlp];
+    int dg[kScanIlp];
 #pragma unroll
-    for (int bin = 0; bin < NBINS; ++bin) {
-      const uint64_t mk = ballot(b == bin);
-      if (lane == 0) bits[bin][word] = mk;
-      if (bin < BIN_LARGE) c[bin] += (unsigned)__popcll(mk);
+    for (int r = 0; r < kScanIlp; ++r) x[r] = look(s0 + r * 64 + lane, s0 + r * 64 + lane < end);
+#pragma unroll
+    for (int r = 0; r < kScanIlp; ++r) {
+      const long long i = s0 + r * 64 + lane;
+      p[r] = want(x[r], i < end);
+      dg[r] = p[r] ? degree(vertex_of(i)) : 0;
     }
-    const int k = (b == BIN_LARGE) ? chunks_of(d, chunk) : 0;
-    c[BIN_LARGE] += (unsigned)wave_sum_i(k);
-    nfv += (unsigned)__popcll(ballot(p));
-    mf += (unsigned long long)wave_sum_ll(p ? d : 0);
+#pragma unroll
+    for (int r = 0; r < kScanIlp; ++r) {
+      if (s0 + r * 64 >= end) break;
+      const long long word = (s0 >> 6) + r;
+      p[r] = keep(word, x[r], s0 + r * 64 + lane < end, p[r], dg[r]);
+      const int d = p[r] ? dg[r] : 0;
+      const int b = p[r] ? bin_of(d, P) : -1;
+#pragma unroll
+      for (int bin = 0; bin < NBINS; ++bin) {
+        const uint64_t mk = ballot(b == bin);
+        if (lane == 0) bits[bin][word] = mk;
+        if (bin < BIN_LARGE) c[bin] += (unsigned)__popcll(mk);
+      }
+      large += (b == BIN_LARGE) ? (unsigned)chunks_of(d, chunk) : 0u;
+      nfv += p[r] ? 1u : 0u;
+      mf += (unsigned long long)d;
+    }
   }
+  c[BIN_LARGE] = (unsigned)wave_sum_i((int)large);
+  nfv = (unsigned)wave_sum_i((int)nfv);
+  mf = (unsigned long long)wave_sum_ll((long long)mf);
   if (lane == 0) {
     for (int bin = 0; bin < NBINS; ++bin) lb.wcnt[wv][bin] = c[bin];
     lb.wnf[wv] = nfv;
@@ -442,19 +466,29 @@ SX_DEV void ballot_fill_range(long long lo, long long hi, unsigned bid, Probe pr
 }
 
 // Positions [0, count) split over the grid in contiguous ranges (multiples
-// of 64 * kWaves); pred(i) is the active test of position i, vertex_of(i)
-// its vertex.
+// of 64 * kWaves): workgroup bid's.
+struct ScanRange {
+  long long lo, hi;
+};
+SX_DEV ScanRange scan_range(const VGrid &vg, int count) {
+  const long long unit = 64 * kWaves;
+  const long long per_wg = (((long long)count + vg.nb - 1) / vg.nb + unit - 1) / unit * unit;
+  const long long lo = (long long)vg.bid * per_wg;
+  return ScanRange{lo, lo + per_wg < count ? lo + per_wg : (long long)count};
+}
+
+// A scan of positions [0, count): pred(i) is the active test of position i,
+// vertex_of(i) its vertex.
 template <class Pred, class Deg, class VertexOf>
 SX_DEV void ballot_fill(const VGrid &vg, int count, Pred pred, Deg degree, VertexOf vertex_of,
                         const Params &P, int chunk, unsigned long long *const bits[NBINS],
                         const Regions &R, RecSlot *rec_slot, LdsBallot &lb) {
-  const long long unit = 64 * kWaves;
-  const long long per_wg = (((long long)count + vg.nb - 1) / vg.nb + unit - 1) / unit * unit;
-  const long long lo = (long long)vg.bid * per_wg;
-  const long long hi = lo + per_wg < count ? lo + per_wg : count;
-  auto probe = [&](long long i, bool ok) { return ok && pred((int)i); };
+  const ScanRange T = scan_range(vg, count);
+  auto look = [&](long long i, bool ok) { return ok && pred((int)i); };
+  auto want = [](bool x, bool) { return x; };
+  auto keep = [](long long, bool, bool, bool p, int) { return p; };
   auto vof = [&](long long i) { return vertex_of((int)i); };
-  ballot_fill_range(lo, hi, vg.bid, probe, degree, vof, P, chunk, bits, R, rec_slot, lb);
+  ballot_fill_range(T.lo, T.hi, vg.bid, look, want, keep, degree, vof, P, chunk, bits, R, rec_slot, lb);
 }
 
 // ------------------------------------------------- worklist traversal ---

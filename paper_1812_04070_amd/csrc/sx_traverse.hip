@@ -64,8 +64,11 @@ struct BfsOps {
     for (int r = 0; r < kIlp; ++r) act[r] = ok[r] && d[r] == -1 && got[r] == -1;
   }
   SX_DEV bool next_active(int v) const { return depth[v] == it + 1; }
-  SX_DEV bool in_frontier(int v) const { return depth[v] == it; }
-  SX_DEV bool pull_candidate(int v) const { return depth[v] == -1; }
+  // pull scan: a vertex's state word, whether it is in the frontier, whether
+  // it may still change
+  SX_DEV int look(int v) const { return depth[v]; }
+  SX_DEV bool listed(int x) const { return x == it; }
+  SX_DEV bool candidate(int x) const { return x == -1; }
 };
 
 struct SsspOps {
@@ -106,8 +109,9 @@ struct SsspOps {
     for (int r = 0; r < kIlp; ++r) act[r] = tr[r] && st[r] != it + 1;
   }
   SX_DEV bool next_active(int v) const { return stamp[v] == it + 1; }
-  SX_DEV bool in_frontier(int v) const { return stamp[v] == it; }
-  SX_DEV bool pull_candidate(int v) const { (void)v; return true; }
+  SX_DEV int look(int v) const { return stamp[v]; }
+  SX_DEV bool listed(int x) const { return x == it; }
+  SX_DEV bool candidate(int x) const { (void)x; return true; }
 };
 
 // Minimum-label propagation: the SSSP relaxation with a zero arc weight (the
@@ -143,8 +147,9 @@ struct WccOps {
     for (int r = 0; r < kIlp; ++r) act[r] = tr[r] && st[r] != it + 1;
   }
   SX_DEV bool next_active(int v) const { return stamp[v] == it + 1; }
-  SX_DEV bool in_frontier(int v) const { return stamp[v] == it; }
-  SX_DEV bool pull_candidate(int v) const { (void)v; return true; }
+  SX_DEV int look(int v) const { return stamp[v]; }
+  SX_DEV bool listed(int x) const { return x == it; }
+  SX_DEV bool candidate(int x) const { (void)x; return true; }
 };
 
 SX_DEV int degree_of(const int *off, int v) { return off[v + 1] - off[v]; }
@@ -383,22 +388,20 @@ SX_PHASE void pull_scan(const VGrid &vg, const TravArgs &a, const Params &P, con
   const Work &w = a.w;
   const int *off = a.g.in_off;
   const int n = a.g.n;
-  {
-    const long long tiles = ((long long)n + 63) / 64;
-    for (long long t = (long long)vg.bid * kWaves + wave_in_wg(); t < tiles;
-         t += (long long)vg.nb * kWaves) {
-      const long long v = t * 64 + lane_id();
-      const bool f = v < n && ops.in_frontier((int)v);
-      const uint64_t mk = ballot(f);
-      if (lane_id() == 0) w.fbits[t] = mk;
-    }
-  }
-  auto pred = [&](int v) { return degree_of(off, v) > 0 && ops.pull_candidate(v); };
   auto deg = [&](int v) { return degree_of(off, v); };
-  auto ident = [](int i) { return i; };
+  auto ident = [](long long i) { return (int)i; };
   const Regions R = regions(w, it & 1, vg.nb);
-  ballot_fill(vg, n, pred, deg, ident, P, 0x7fffffff, w.bits, R,
-              w.rec + SLOT_SCAN, lds.ball);
+  // one pass over the state: a tile's frontier word with its candidates
+  const ScanRange T = scan_range(vg, n);
+  auto look = [&](long long i, bool ok) { return ok ? ops.look((int)i) : 0; };
+  auto want = [&](int x, bool ok) { return ok && ops.candidate(x); };
+  auto keep = [&](long long word, int x, bool ok, bool p, int d) {
+    const uint64_t mk = ballot(ok && ops.listed(x));
+    if (lane_id() == 0) w.fbits[word] = mk;
+    return p && d > 0;
+  };
+  ballot_fill_range(T.lo, T.hi, vg.bid, look, want, keep, deg, ident, P, 0x7fffffff, w.bits, R, w.rec + SLOT_SCAN,
+                    lds.ball);
 }
 
 SX_DEV bool fbit(const unsigned long long *fb, int u) { return (fb[u >> 6] >> (u & 63)) & 1ull; }
