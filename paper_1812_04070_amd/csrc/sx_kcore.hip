@@ -7,9 +7,9 @@
 //   Active   alive and degree <= k.
 //   Compute  deleting v lowers the degree of each neighbour by one.
 //   Combine  sum (aggregation).  Push: an atomic decrement per arc; following
-//            the paper's k-core note, a neighbour whose degree is already
-//            <= k is not decremented any more (it is deleted at this level
-//            anyway).  Pull: every alive vertex counts its neighbours deleted
+//            the paper's k-core note, a neighbour that already has its core
+//            number (degree <= k: it is deleted at this level anyway) is
+//            not decremented any more.  Pull: every alive vertex counts its neighbours deleted
 //            in this step and lowers its own degree once, without atomics.
 //            A vertex is activated by the update that takes its degree from
 //            above k to k or below, so it enters a frontier exactly once.
@@ -28,9 +28,8 @@
 // Direction (Section 5, switching to pull for large frontiers): a step pulls
 // when the frontier's arcs exceed the alive arcs / kPullAlpha.  In R-MAT
 // graphs the dense last levels delete thousands of high-degree vertices per
-// step; pushing them costs one device-scope atomic per arc (MI355X sustains
-// ~13 G/s of them over scattered addresses) while a pull step reads the
-// alive arcs at memory speed.  A directed graph counts in- plus out-arcs and
+// step; pushing them costs one device-scope atomic per arc (at most 27 G/s)
+// while a pull step reads the alive arcs and their stamps.  A directed graph counts in- plus out-arcs and
 // walks both its CSR and CSC rows.
 #include "sx_frontier.hpp"
 #include "sx_kernels.hpp"
@@ -45,7 +44,12 @@ namespace sx {
 // activation test needs only the value before and after each atomic.
 constexpr int kHot = 4096;         // table entries (power of two, 32 KB of LDS)
 constexpr int kHotProbes = 8;
-constexpr int kHotDeg = 64;        // current degree from which a target is summed
+constexpr int kHotDeg = 64;        // row length from which a target may be summed
+// ... and only targets that the step is expected to hit this often, by their
+// row's share of the alive arcs: a table that every target of a dense level
+// competes for is full of vertices seen once (R-MAT s22, whole run: threshold
+// 64 arcs 17.9 ms, 4 expected hits 17.5, 16 hits 17.2, 32 hits 17.2)
+constexpr float kHotHits = 16.f;
 constexpr unsigned long long kHotMinArcs = 65536;  // steps below this push directly
 // Local cascades: a vertex that a push step activates is deleted by the same
 // workgroup within the same step when its degree is below kLocalDeg and the
@@ -60,7 +64,12 @@ constexpr unsigned long long kHotMinArcs = 65536;  // steps below this push dire
 constexpr int kLocalDeg = 256;
 constexpr int kLocalQ = 2048;
 constexpr unsigned kLocalArcs = 8192;   // arcs a workgroup takes on locally per step
-constexpr float kPullAlpha = 8.f;  // pull when frontier arcs > alive arcs / alpha
+// Pull when the step's arcs exceed the alive arcs / alpha: pull steps read the
+// alive rows and one stamp per arc at ~100 G arcs/s, push steps reach 40-80
+// G arcs/s of their own rows (their dead and summed targets included).  R-MAT
+// s22, whole run: alpha 8 17.2 ms, 5 and 3.5 16.5, 2 16.3, 0.5 16.5; 16 and more 17.8
+// to 21.8.
+constexpr float kPullAlpha = 4.f;
 
 struct LdsK {
   int hkey[kHot];
@@ -193,7 +202,7 @@ SX_DEV unsigned alive_min_degree(const VGrid &vg, const Work &w, int p, LdsK &ld
 // their neighbours; activated neighbours form the list of step j + 1 (online
 // filter into slot (j + 1) % 3, parity (j + 1) & 1).
 SX_DEV void kpeel_push(const VGrid &vg, const KArgs &a, int k, int j, const ViewRef &cur,
-                       const Totals &T, LdsK &lds) {
+                       const Totals &T, unsigned long long alive_arcs, LdsK &lds) {
   const Work &w = a.w;
   const DevGraph &g = a.g;
   const unsigned cs = T.cnt[BIN_SMALL], cm = T.cnt[BIN_MED], cl = T.cnt[BIN_LARGE];
@@ -221,7 +230,8 @@ SX_DEV void kpeel_push(const VGrid &vg, const KArgs &a, int k, int j, const View
     const unsigned h = ((unsigned)u * 2654435761u) >> 20;
     for (int p = 0; p < kHotProbes; ++p) {
       const unsigned s = (h + (unsigned)p) & (kHot - 1);
-      const int prev = atomicCAS(&lds.hkey[s], -1, u);
+      int prev = lds.hkey[s];
+      if (prev == -1) prev = atomicCAS(&lds.hkey[s], -1, u);
       if (prev == -1 || prev == u) {
         atomicAdd(&lds.hcnt[s], 1);
         if (prev == -1) lds.hlist[atomicAdd(&lds.hn, 1u)] = (unsigned short)s;
@@ -259,18 +269,27 @@ SX_DEV void kpeel_push(const VGrid &vg, const KArgs &a, int k, int j, const View
     bins_append(act && !local, u, du, NR, vg.bid, a.P, a.P.chunk, lds.bins, st);
   };
   bool use_hot = hot;
-  // kIlp arcs per lane: all degree loads, then all decrements, then the
-  // degrees of the activated targets, each stage with every arc in flight
+  const float hot_row = kHotHits * (float)alive_arcs / (float)(T.mf ? T.mf : 1);
+  const int hot_deg = hot_row > 1e9f ? 1000000000 : hot_row > (float)kHotDeg ? (int)hot_row : kHotDeg;
+  // kIlp arcs per lane: all core numbers, then all decrements, then the
+  // degrees of the activated targets, each stage with every arc in flight.
+  // The target's state is read from its core number and its row length, which
+  // no atomic touches: plain loads of the current degrees, between the atomics
+  // on the same lines, held both back (2^17 words: 10 G/s mixed, 27 G/s
+  // atomics alone).  A target below k that is still alive costs an atomic.
+  // R-MAT s22: pushes of 50 us and more 9.1 -> 6.5 ms with kHotHits
   auto op = [&](const int *v, const int *u, const int *arc, const bool *ok) {
     (void)v; (void)arc;
-    int d[kIlp], old[kIlp], du[kIlp];
+    int row[kIlp], old[kIlp], du[kIlp];
     bool dec[kIlp], act[kIlp];
 #pragma unroll
-    for (int r = 0; r < kIlp; ++r) d[r] = ok[r] ? deg[u[r]] : 0;  // stale (higher) costs an atomic
+    for (int r = 0; r < kIlp; ++r) dec[r] = ok[r] && a.core[u[r]] == -1;
+#pragma unroll
+    for (int r = 0; r < kIlp; ++r) row[r] = use_hot && dec[r] ? total_degree(g, u[r]) : 0;
 #pragma unroll
     for (int r = 0; r < kIlp; ++r) {
       edges += ok[r] ? 1 : 0;
-      dec[r] = ok[r] && d[r] > k && !(use_hot && d[r] >= kHotDeg && hot_add(u[r]));
+      dec[r] = dec[r] && !(row[r] >= hot_deg && hot_add(u[r]));
     }
 #pragma unroll
     for (int r = 0; r < kIlp; ++r) old[r] = dec[r] ? atomic_sub_i32(&deg[u[r]], 1) : 0;
@@ -504,7 +523,7 @@ SX_DEV void kpeel(const VGrid &vg, const KArgs &a, const KState &q, bool pull, b
   } else {
     if (!have)
       T = kview(vg, a.w, q.from_scan ? SLOT_SCAN : q.j % 3, regions(a.w, q.j & 1, vg.nb), lds, ref);
-    kpeel_push(vg, a, q.k, q.j, ref, T, lds);
+    kpeel_push(vg, a, q.k, q.j, ref, T, q.alive_arcs, lds);
   }
 }
 
