@@ -61,9 +61,14 @@ constexpr unsigned long long kHotMinArcs = 65536;  // steps below this push dire
 // grid-wide steps without this, most of them with a handful of vertices and
 // each paying a launch and a record prefix.  Every vertex is still deleted
 // exactly once (by the update that activated it), so the result is the same.
-constexpr int kLocalDeg = 256;
+// A light step (below kHotMinArcs) leaves most workgroups idle, so it takes on
+// longer rows and twice the arcs: the dense levels' vertices have rows of 290
+// and more, and their chains ended in steps of a handful of vertices (R-MAT
+// s22: 720 -> 608 launches, 16.8 -> 16.0 ms; rows of 1,024 in heavy steps too
+// 16.1, of 4,096 in light ones 16.7).
+constexpr int kLocalDeg = 256, kLocalDegLight = 1024;
 constexpr int kLocalQ = 2048;
-constexpr unsigned kLocalArcs = 8192;   // arcs a workgroup takes on locally per step
+constexpr unsigned kLocalArcs = 8192, kLocalArcsLight = 16384;   // per workgroup and step
 // Pull when the step's arcs exceed the alive arcs / alpha: pull steps read the
 // alive rows and one stamp per arc at ~100 G arcs/s, push steps reach 40-80
 // G arcs/s of their own rows (their dead and summed targets included).  R-MAT
@@ -243,8 +248,10 @@ SX_DEV void kpeel_push(const VGrid &vg, const KArgs &a, int k, int j, const View
   // An activated vertex u (degree du): into the local queue (deleted in this
   // step, stamp j) or the next step's list (stamp j + 1).  Called
   // convergently by whole wavefronts.
+  const int local_deg = hot ? kLocalDeg : kLocalDegLight;
+  const unsigned local_arcs = hot ? kLocalArcs : kLocalArcsLight;
   auto activate = [&](bool act, int u, int du) {
-    const bool want = act && du < kLocalDeg;
+    const bool want = act && du < local_deg;
     const uint64_t mk = ballot(want);
     bool local = false;
     if (mk) {
@@ -260,7 +267,7 @@ SX_DEV void kpeel_push(const VGrid &vg, const KArgs &a, int k, int j, const View
         const unsigned pos = base + lane_prefix(mk);
         if (pos < (unsigned)kLocalQ) {
           // a reserved slot is always written: -1 (skipped) when over budget
-          local = abase + (unsigned)incl <= kLocalArcs;
+          local = abase + (unsigned)incl <= local_arcs;
           lds.lq[pos] = local ? u : -1;
         }
       }
