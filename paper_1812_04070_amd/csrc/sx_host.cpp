@@ -50,6 +50,7 @@ static sx_status fail(sx_status s, const char *fmt, ...) {
 static constexpr int kSeqHintMargin = 2;
 // Sequenced k-core grid for graphs up to 2^23 vertices and 2^28 arcs
 static constexpr int kKcoreSmallGrid = 256;
+static constexpr long long kMarkArcs = 6000000;
 static constexpr long long kKcoreSmallN = 1ll << 23;
 static constexpr long long kKcoreSmallArcs = 1ll << 28;
 
@@ -971,6 +972,12 @@ static sx_status run_traversal(sx_program *p, sx_graph *G, int src, void *d_out,
       a.cascade_window = p->ap.sssp_delta == SX_DELTA_AUTO ? std::max(1u, a.P.delta / 5) : a.P.delta;
     }
   }
+  // SSSP steps of a quarter of the arcs and more only mark what they improve
+  // (SsspOps::mark).  A half to a sixteenth measured the same within 1 %; the
+  // scan and its launch cost more than the lists below some 6 M arcs (R-MAT
+  // s16 0.336 -> 0.350 ms, s17 0.358 -> 0.361, s18 with 7.6 M arcs 0.485 ->
+  // 0.465, s20 0.96 -> 0.86).
+  if (sequenced && algo == ALG_SSSP && engine_schedules(p->pol) && G->g.m >= kMarkArcs) a.mark_share = 4;
   // every WCC vertex starts active: unless the caller forces push, the first
   // iteration pulls; a push start builds its lists with a ballot scan
   const bool pull_first = p->pol.direction == SX_DIR_PULL || (wcc && p->pol.direction == SX_DIR_AUTO);

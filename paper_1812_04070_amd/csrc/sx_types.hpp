@@ -166,6 +166,9 @@ struct TravArgs {
   // distances (SSSP)
   int cascade_after;
   unsigned cascade_window;
+  // sequenced SSSP: a push of a mark_share-th of the arcs or more leaves the
+  // next lists to a ballot scan (0: never)
+  unsigned mark_share;
 };
 
 // Iterations after which a BFS / an SSSP may go over to the cascade, and the
