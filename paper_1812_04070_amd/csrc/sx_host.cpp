@@ -976,7 +976,8 @@ static sx_status run_traversal(sx_program *p, sx_graph *G, int src, void *d_out,
   // (SsspOps::mark).  A half to a sixteenth measured the same within 1 %; the
   // scan and its launch cost more than the lists below some 6 M arcs (R-MAT
   // s16 0.336 -> 0.350 ms, s17 0.358 -> 0.361, s18 with 7.6 M arcs 0.485 ->
-  // 0.465, s20 0.96 -> 0.86).
+  // 0.465, s20 0.96 -> 0.86).  Under the learned policy too: the step after a
+  // marked one is a push, which it is not asked about.
   if (sequenced && algo == ALG_SSSP && engine_schedules(p->pol) && G->g.m >= kMarkArcs) a.mark_share = 4;
   // every WCC vertex starts active: unless the caller forces push, the first
   // iteration pulls; a push start builds its lists with a ballot scan
