@@ -1201,7 +1201,8 @@ SX_DEV bool seq_body(const TravArgs &a, unsigned L, LdsTrav &lds, LdsPolicy &pol
       {
         bool mark = false;
         if constexpr (std::is_same<Ops, SsspOps>::value) {
-          mark = s.B == 0xFFFFFFFFu && T.mf * a.mark_share >= (unsigned long long)a.g.m;
+          // (an edgeless graph's empty lists must reach a decision)
+          mark = a.mark_share && s.B == 0xFFFFFFFFu && T.mf * a.mark_share >= (unsigned long long)a.g.m;
           ops.mark = mark;
         }
         push_phase(vg, a, s.P, ops, it, ref, T, lds, s.B);
