@@ -1052,8 +1052,9 @@ __global__ void __launch_bounds__(kBlock) k_pull_step(TravArgs a, int it) {
 // MI355X, against ~6-10 us for a software barrier over a full persistent
 // grid) per phase, and each phase at the occupancy of its own registers.
 // seq line: [0] phase [1] iteration [2,3] unexplored arcs [4] previous
-// frontier size [6,7] activated so far [8] t1 [9] t2 [10] pulling [11] a
-// decision is due [12] the push lists come from a ballot scan [13] the
+// frontier size [6,7] activated so far [8] t1 [9] t2 [10] pulling [11] 1: a
+// decision is due; 2: the scan lists what a marking step improved, whose count
+// no decision has seen [12] the push lists come from a ballot scan [13] the
 // delta-stepping bound (0: not set yet) [14] buckets dropped (pull steps)
 SX_DEV void seq_store(Line &l, unsigned phase, const RunState &s, unsigned pulling, unsigned due,
                       unsigned rebuilt) {
@@ -1134,7 +1135,16 @@ SX_DEV bool seq_body(const TravArgs &a, unsigned L, LdsTrav &lds, LdsPolicy &pol
   ViewRef ref;
   Totals T;
   bool have_view = false;
-  if (due) {
+  // the run ends with this launch's decision
+  auto ends = [&]() {
+    if (!lead) return;
+    seq_store(out, s.it >= a.P.max_iters ? SEQ_LIMIT : SEQ_DONE, s, pulling, 0, 0);
+    // the run needed launches 0..L: the host sizes the next run's first
+    // batch of launches on this graph by it (Ctrl::stats word 12, unused
+    // by the other programs; k_trav_init clears it)
+    store_relaxed(&C->stats.v[12], L + 1u);
+  };
+  if (due == 1) {
     T = make_view(vg, a, (s.it + 1) % 3, (s.it + 1) & 1, lds, ref);
     // one launch per phase: the weights are staged only by a launch whose
     // decision evaluates the network
@@ -1142,13 +1152,7 @@ SX_DEV bool seq_body(const TravArgs &a, unsigned L, LdsTrav &lds, LdsPolicy &pol
     Decision d = decide<Ops>(a, s, pulling != 0, T, &pol, vg.bid == 0, true);
     if (d.done) {
       ++s.it;
-      if (lead) {
-        seq_store(out, s.it >= a.P.max_iters ? SEQ_LIMIT : SEQ_DONE, s, pulling, 0, 0);
-        // the run needed launches 0..L: the host sizes the next run's first
-        // batch of launches on this graph by it (Ctrl::stats word 12, unused
-        // by the other programs; k_trav_init clears it)
-        store_relaxed(&C->stats.v[12], L + 1u);
-      }
+      ends();
       return true;
     }
     // delta-stepping: once no listed vertex lies below the bound, move it to
@@ -1197,6 +1201,16 @@ SX_DEV bool seq_body(const TravArgs &a, unsigned L, LdsTrav &lds, LdsPolicy &pol
         T = make_view(vg, a, rebuilt ? SLOT_SCAN : it % 3, it & 1, lds, ref);
         if (rebuilt && !scan_fits(a, T)) break;
       }
+      if (due == 2) {
+        // after a marking step: the end, and the counts that a later decision
+        // goes by (the direction is not open, see mark)
+        if (T.nf == 0 || s.it >= a.P.max_iters) {
+          ends();
+          return true;
+        }
+        s.ps.nf_prev = T.nf;
+        s.ps.reached += T.nf;
+      }
       if (lead) atomic_add_u32(&C->stats.v[6], 1u);
       {
         bool mark = false;
@@ -1206,14 +1220,14 @@ SX_DEV bool seq_body(const TravArgs &a, unsigned L, LdsTrav &lds, LdsPolicy &pol
           ops.mark = mark;
         }
         push_phase(vg, a, s.P, ops, it, ref, T, lds, s.B);
-        if (lead) seq_store(out, mark ? PH_BALLOT : PH_PUSH, s, 0, mark ? 0 : 1, 0);
+        if (lead) seq_store(out, mark ? PH_BALLOT : PH_PUSH, s, 0, mark ? 2 : 1, 0);
       }
       break;
     case PH_BALLOT:
       // rebuild the lists of it+1, then push them
       ballot_next(vg, a, s.P, ops, it, lds);
       ++s.it;
-      if (lead) seq_store(out, PH_PUSH, s, 0, 0, 1);
+      if (lead) seq_store(out, PH_PUSH, s, 0, due == 2 ? 2 : 0, 1);
       break;
     case PH_PULL_SCAN:
       if (lead) atomic_add_u32(&C->stats.v[6], 1u);
