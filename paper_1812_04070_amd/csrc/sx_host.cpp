@@ -684,10 +684,13 @@ static sx_status ctrl_error(const Ctrl *c) {
 // Enqueue the mapping of a renumbered run's result into the caller's array.  A
 // run that knows its last kernel does so before it waits for the device: a
 // wait of its own for this one kernel cost 15 to 30 us a run (R-MAT s22 BFS
-// 364 -> 348 us, s20 PageRank to a tolerance 1,726 -> 1,698 us).
-static sx_status map_back(sx_graph *G, hipStream_t st) {
+// 364 -> 348 us, s20 PageRank to a tolerance 1,726 -> 1,698 us).  A run that
+// failed leaves the caller's array as it was (belief propagation's priors
+// among them), and one that is not over when the mapping's turn comes
+// (*phase, a device word, is not `end`) is mapped again later.
+static sx_status map_back(sx_graph *G, hipStream_t st, const unsigned *phase = nullptr, unsigned end = 0) {
   if (G->out && !G->mapped) {
-    HIP_TRY(reorder_unpermute(G->state, G->d_inv, G->out, G->g.n, st));
+    HIP_TRY(reorder_unpermute(G->state, G->d_inv, G->out, G->g.n, &G->w.ctrl->error.v[0], phase, end, st));
     G->mapped = true;
   }
   return SX_OK;
@@ -718,7 +721,7 @@ static sx_status seq_drive(sx_graph *G, hipStream_t st, int first, int maxb, uns
     for (int k = 0; k < batch; ++k) HIP_TRY(launch(L++));
     launches += batch;
     if (ends_first && L == (unsigned)batch) {
-      sx_status m = map_back(G, st);
+      sx_status m = map_back(G, st, &G->w.ctrl->seq[L & 1].v[0], SEQ_DONE);
       if (m != SX_OK) return m;
       HIP_TRY(hipEventRecord(G->ev1, st));
     }
@@ -745,7 +748,7 @@ static sx_status seq_drive(sx_graph *G, hipStream_t st, int first, int maxb, uns
       if (ended_first) *ended_first = ends_first && !piped;
       return SX_OK;
     }
-    G->mapped = false;   // mapped before its end, if at all
+    G->mapped = false;   // not over: nothing was written
     if (L > limit) return fail(SX_EHIP, "run did not converge");
     if (!piped) {
       // second and third batch: from here on one batch stays in flight
@@ -1316,7 +1319,8 @@ static sx_status run_pagerank(sx_program *p, sx_graph *G, void *d_out, hipStream
     HIP_TRY(pagerank_launch(a, grid, st));
   }
   int launches = 2;
-  sx_status s = map_back(G, st);
+  // (until stable: the pull kernel may leave the end to the push kernel)
+  sx_status s = conv ? map_back(G, st, &G->w.ctrl->state.v[0], EXIT_DONE) : map_back(G, st);
   if (s != SX_OK) return s;
   HIP_TRY(hipEventRecord(G->ev1, st));
   if (conv) {
@@ -1804,7 +1808,7 @@ extern "C" sx_status sx_run(sx_program *p, const sx_graph *gc, int32_t source, v
   }
   if (s != SX_OK || !G->reordered || G->mapped) return s;
   HIP_TRY(hipEventRecord(G->ev0, st));
-  HIP_TRY(reorder_unpermute(G->state, G->d_inv, d_out, n, st));
+  HIP_TRY(reorder_unpermute(G->state, G->d_inv, d_out, n, nullptr, nullptr, 0, st));
   HIP_TRY(hipEventRecord(G->ev1, st));
   HIP_TRY(hipEventSynchronize(G->ev1));
   float ms = 0.f;

@@ -70,7 +70,8 @@ using RkAlloc = std::function<hipError_t(void **, size_t)>;
 hipError_t reorder_build(const DevGraph &g, const RkAlloc &own, const RkAlloc &tmp, hipStream_t s,
                          DevGraph &out, int **d_inv, int *h_inv);
 // out[v] = in[inv[v]] for 4-byte elements
-hipError_t reorder_unpermute(const void *in, const int *inv, void *out, int n, hipStream_t s);
+hipError_t reorder_unpermute(const void *in, const int *inv, void *out, int n, const unsigned *error,
+                             const unsigned *phase, unsigned end, hipStream_t s);
 // out[inv[v]] = in[v] for 4-byte elements
 hipError_t reorder_permute(const void *in, const int *inv, void *out, int n, hipStream_t s);
 

@@ -67,8 +67,13 @@ __global__ void k_rk_rows(const int *off, const int *idx, const unsigned *w, con
   }
 }
 
-// out[v] = in[inv[v]]: a result in the new numbering back to the caller's
-__global__ void k_rk_unpermute(const unsigned *in, const int *inv, unsigned *out, int n) {
+// out[v] = in[inv[v]]: a result in the new numbering back to the caller's.
+// Enqueued before the host knows how the run ended, so the run's words decide:
+// nothing is written after an error, nor while *phase is not `end` (NULL: the
+// run is known to be over).
+__global__ void k_rk_unpermute(const unsigned *in, const int *inv, unsigned *out, int n, const unsigned *error,
+                               const unsigned *phase, unsigned end) {
+  if ((error && *error) || (phase && *phase != end)) return;
   for (long long v = (long long)blockIdx.x * blockDim.x + threadIdx.x; v < n;
        v += (long long)gridDim.x * blockDim.x)
     out[v] = in[inv[v]];
@@ -189,10 +194,11 @@ hipError_t reorder_build(const DevGraph &g, const RkAlloc &own, const RkAlloc &t
   return hipSuccess;
 }
 
-hipError_t reorder_unpermute(const void *in, const int *inv, void *out, int n, hipStream_t s) {
+hipError_t reorder_unpermute(const void *in, const int *inv, void *out, int n, const unsigned *error,
+                             const unsigned *phase, unsigned end, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_rk_unpermute, dim3(rk_grid(n)), dim3(kRkBlock), 0, s, (const unsigned *)in, inv,
-                     (unsigned *)out, n);
+                     (unsigned *)out, n, error, phase, end);
   return hipGetLastError();
 }
 

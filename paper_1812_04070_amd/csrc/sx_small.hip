@@ -175,7 +175,9 @@ __global__ void __launch_bounds__(kSmBlock) k_small(TravArgs a, int *out, const 
   const unsigned ew = (unsigned)wave_sum_i((int)edges);
   if (lane == 0) atomicAdd(&S.edges, (unsigned long long)ew);
   __syncthreads();
-  for (int v = t; v < n; v += kSmBlock) out[v] = (int)S.dist[inv ? inv[v] : v];
+  // (a failed run leaves the caller's array)
+  if (!S.err)
+    for (int v = t; v < n; v += kSmBlock) out[v] = (int)S.dist[inv ? inv[v] : v];
   if (t == 0) {
     C->state.v[0] = EXIT_DONE;
     C->stats.v[6] = it;
