@@ -28,22 +28,26 @@ __global__ void __launch_bounds__(kCasBlock) k_cascade(TravArgs a, unsigned L) {
     return;
   }
   const unsigned now = step % 3, nxt = (step + 1) % 3;
-  const unsigned cnt = aux[8 + now], lowest = aux[12 + now], left = aux[16 + now], hubs = aux[24 + now];
+  const unsigned cnt = aux[8 + now], lowest = aux[12 + now], hubs = aux[24 + now];
   if (cnt + hubs == 0) {
     // the run is over; BFS counts its levels (the depths reached)
     if (!kWeighted) cas_levels<kCasBlock>(hw_grid(), a);
     if (blockIdx.x == 0 && t < 32) store_relaxed(&out.v[t], t == 0 ? (unsigned)SEQ_DONE : in[t]);
     return;
   }
-  // BFS: a list this long is the business of the level phases, which rebuild
-  // it from the depths (unless vertices were left over or carried, every
-  // listed vertex has the last window's end as its depth, or a smaller one
-  // from which it has been expanded)
-  if (!kWeighted && cnt > kCasMaxList && left == 0) {
+  // back to the phases: a ballot scan after iteration it - 1, then iteration `it`
+  if (cas_outgrown(cnt, in[17])) {
+    const unsigned it = kWeighted ? in[1] + 2u : lowest;
+    cas_way_back<kWeighted, kCasBlock>(hw_grid(), a, cnt, hubs, in[19] & 1u, lowest, (int)it);
     if (blockIdx.x == 0 && t < 32) {
-      const unsigned x = t == 0 ? (unsigned)PH_BALLOT : t == 1 ? lowest - 1u : t == 11 || t == 12 ? 0u : in[t];
+      // [13] buckets go on at the one that holds the smallest distance
+      const unsigned long long nb = kWeighted && a.P.delta ? ((unsigned long long)lowest / a.P.delta + 1ull) * a.P.delta : 0ull;
+      const unsigned bound = in[13] == 0xFFFFFFFFu || nb >= 0xFFFFFFFFull ? 0xFFFFFFFFu : (unsigned)nb;
+      const unsigned x = t == 0 ? (unsigned)PH_BALLOT : t == 1 ? it - 1u : t == 11 ? 3u : t == 12 ? 0u
+                       : t == 13 && kWeighted ? bound : t == 15 ? it + (unsigned)kCasHold : in[t];
       store_relaxed(&out.v[t], x);
-      if (t == 6) store_relaxed(&C->stats.v[6], lowest);   // levels done
+      if (!kWeighted && t == 6) store_relaxed(&C->stats.v[6], lowest);   // levels done
+      if (kWeighted && t < 3) store_relaxed(&C->aux.v[t], 0xFFFFFFFFu);  // smallest distances of the steps to come
     }
     return;
   }

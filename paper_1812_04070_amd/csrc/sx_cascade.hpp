@@ -35,11 +35,18 @@
 // scale 12-17 and grids of side 128 and 512: 20.0 -> 3.8 ms.
 //
 // An improved vertex that finds its workgroup's queue full goes to the next
-// list too (a leftover), and so does a vertex of kCasHub arcs or more, whose
+// list too, and so does a vertex of kCasHub arcs or more, whose
 // row the next step spreads over all workgroups.  A vertex enters a list
 // once per step (stamp), so a list holds at most n entries; a listed vertex
 // is expanded from its current value when that lies below B, whatever put it
 // there.
+//
+// A list that outgrows the cascade (cas_outgrown) goes back to the level phases
+// (cas_way_back): it has met a part of the graph of low diameter, where a
+// window of unsynchronised relaxations does most of its work many times over.
+// Random graph of 3 M vertices and 6 arcs each behind a path of 20: BFS in
+// phases alone 0.94 ms, without the way back for lists with leftovers 5.0, with
+// it 1.1; SSSP (window of 8 mean weights) 3.0 / 11.1 / 3.7.
 #pragma once
 
 #include "sx_frontier.hpp"
@@ -52,7 +59,9 @@ constexpr int kCasQ = 256;             // LDS queue entries (two queues)
 constexpr int kCasFar = 512;           // listed vertices gathered in LDS
 constexpr int kCasLane = 16;           // arcs up to which four lanes walk a row
 constexpr int kCasHub = 4096;          // and from which the grid does
-constexpr unsigned kCasMaxList = 1u << 16;  // BFS: longer lists go back to the levels
+constexpr unsigned kCasMaxList = 1u << 16;  // longer lists go back to the phases
+constexpr int kCasJump = 2048;         // and lists that jump beyond 4 times the last by this
+constexpr int kCasHold = 16;           // ... for this many iterations at least
 
 typedef int Arcs4 __attribute__((ext_vector_type(4), aligned(4)));
 
@@ -63,7 +72,7 @@ struct LdsCas {
   uint4 qw[2][kWeighted ? kCasQ : 1];  // and their arcs' weights
   int far[kCasFar];
   unsigned in[64];                     // run state and control words
-  unsigned qn[3], fn, base, low, late, err;
+  unsigned qn[3], fn, base, low, err;
   unsigned long long edges;
 };
 
@@ -81,7 +90,7 @@ SX_DEV unsigned cas_append(bool on, unsigned *count) {
 template <bool kWeighted>
 SX_DEV void cas_begin(LdsCas<kWeighted> &S) {
   if (threadIdx.x == 64) {
-    S.qn[0] = S.qn[1] = S.qn[2] = S.fn = S.late = S.err = 0u;
+    S.qn[0] = S.qn[1] = S.qn[2] = S.fn = S.err = 0u;
     S.low = 0xFFFFFFFFu;
     S.edges = 0ull;
   }
@@ -108,10 +117,17 @@ SX_DEV unsigned cas_window(unsigned window, unsigned cnt, unsigned before, unsig
   return window * 2 < most ? window * 2 : most;
 }
 
+// Whether a list is the phases' business: long, or many times the one before
+// (meshes' lists grow by half a step at most; a blob's first vertices overflow
+// one workgroup's queue, and the next step would walk all of it unsynchronised).
+SX_DEV bool cas_outgrown(unsigned cnt, unsigned before) {
+  return cnt > kCasMaxList || cnt > 4u * before + (unsigned)kCasJump;
+}
+
 // One step: the `cnt` vertices listed in reg_s[par] and the `hubs` in
 // reg_m[par], up to distance B.  Ctrl::aux, by step number s % 3 (`nxt`: of
-// s + 1): words 8.. the list's length, 12.. its smallest distance, 16..
-// workgroups with leftovers or carried vertices, 24.. hubs listed.  `tag`: a
+// s + 1): words 8.. the list's length, 12.. its smallest distance, 24.. hubs
+// listed.  `tag`: a
 // stamp no other step and no iteration of the run uses.  The graph has at least
 // four arcs.
 template <bool kWeighted, int kThreads>
@@ -130,12 +146,11 @@ SX_DEV void cascade_step(const VGrid &vg, const TravArgs &a, LdsCas<kWeighted> &
   const int *off = a.g.off, *idx = a.g.idx;
   const unsigned *wt = a.g.w;
   unsigned low = 0xFFFFFFFFu, err = 0, edges = 0, ents = 0;
-  bool late = false;                        // a leftover or a carried vertex
   // u (a row of `len` arcs) into the next launch's list; whole wavefront
   auto list_append = [&](bool on, int u, unsigned d, int len) {
     if (!ballot(on)) return;
+    low = on && d < low ? d : low;   // also of a vertex that is listed already
     on = on && atomic_exch_i32(&a.w.stamp[u], tag) != tag;
-    low = on && d < low ? d : low;
     const bool hub = on && len >= kCasHub;
     if (hub) a.w.reg_m[par ^ 1u][atomic_add_u32(&C->aux.v[24 + nxt], 1u)] = u;
     on = on && !hub;
@@ -174,7 +189,6 @@ SX_DEV void cascade_step(const VGrid &vg, const TravArgs &a, LdsCas<kWeighted> &
       }
       full = near && pos >= (unsigned)kCasQ;
     }
-    late = late || hub || full;
     list_append(far || hub || full, u, d, re - rb);
   };
   // one arc per lane, to u at distance d + w: the offsets of u's row and the
@@ -254,7 +268,6 @@ SX_DEV void cascade_step(const VGrid &vg, const TravArgs &a, LdsCas<kWeighted> &
     const unsigned d = load_relaxed(&dist[v]);
     const int rb = off[v], re = off[v + 1];
     if (d >= B) {
-      late = true;
       if (vg.bid == 0) list_append(t == 0, v, d, re - rb);
       continue;
     }
@@ -276,7 +289,6 @@ SX_DEV void cascade_step(const VGrid &vg, const TravArgs &a, LdsCas<kWeighted> &
       int4 ids;
       uint4 ws;
       first_arcs(rb, ids, ws);
-      late = late || (ok && d >= B);
       enqueue(ok && d < B, ok && d >= B, v, d, rb, re, ids, ws, (int)(round & 1u), &S.qn[round % 3]);
     }
     __syncthreads();
@@ -286,10 +298,9 @@ SX_DEV void cascade_step(const VGrid &vg, const TravArgs &a, LdsCas<kWeighted> &
   // this workgroup's part of the next list
   low = wave_min_u(low);
   const unsigned ew = (unsigned)wave_sum_i((int)edges);
-  const bool any_late = ballot(late) != 0, any_err = ballot(err != 0) != 0;
+  const bool any_err = ballot(err != 0) != 0;
   if (lane_id() == 0) {
     if (low != 0xFFFFFFFFu) atomicMin(&S.low, low);
-    if (any_late) S.late = 1u;
     if (any_err) S.err = 1u;
     atomicAdd(&S.edges, (unsigned long long)ew);
   }
@@ -298,7 +309,6 @@ SX_DEV void cascade_step(const VGrid &vg, const TravArgs &a, LdsCas<kWeighted> &
   if (t == 0) {
     if (fn) S.base = atomic_add_u32(&C->aux.v[8 + nxt], fn);
     if (S.low != 0xFFFFFFFFu) atomic_min_u32(&C->aux.v[12 + nxt], S.low);
-    if (S.late) atomic_add_u32(&C->aux.v[16 + nxt], 1u);
     if (S.err) store_relaxed(&C->error.v[0], (unsigned)SX_ERR_OVERFLOW);
     Line &l = C->statw[vg.bid % kStatLines];
     atomic_add_u64((unsigned long long *)&l.v[0], S.edges);
@@ -314,8 +324,44 @@ SX_DEV void cas_clear(Ctrl *C, unsigned step, int t) {
   const unsigned clr = (step + 2) % 3;
   if (t == 0) store_relaxed(&C->aux.v[8 + clr], 0u);
   if (t == 1) store_relaxed(&C->aux.v[12 + clr], 0xFFFFFFFFu);
-  if (t == 2) store_relaxed(&C->aux.v[16 + clr], 0u);
-  if (t == 3) store_relaxed(&C->aux.v[24 + clr], 0u);
+  if (t == 2) store_relaxed(&C->aux.v[24 + clr], 0u);
+}
+
+// The run as the phases know it, in place of a step: `cnt` vertices listed in
+// reg_s[par], `hubs` in reg_m[par], the smallest value `lowest` (the phases'
+// next iteration is `it`, which the caller chose: BFS `lowest`).  What lies at
+// `lowest` or below is final, and every pending vertex is listed.
+//   BFS   Deeper vertices are unvisited again (their depths may be too long,
+//         and the phases take a depth for final), the vertices at `lowest` are
+//         the frontier.  Ctrl::aux words 28, 29 add up the arcs of the visited
+//         ones: the rest is unexplored, which the direction rule goes by.
+//   SSSP  The listed vertices are the frontier (stamp `it`).
+// The lists then come from a ballot scan.
+template <bool kWeighted, int kThreads>
+SX_DEV void cas_way_back(const VGrid &vg, const TravArgs &a, unsigned cnt, unsigned hubs, unsigned par,
+                         unsigned lowest, int it) {
+  const long long tid = (long long)vg.bid * kThreads + threadIdx.x, nt = (long long)vg.nb * kThreads;
+  if constexpr (kWeighted) {
+    for (long long i = tid; i < cnt; i += nt) {
+      const int v = a.w.reg_s[par][i];
+      if ((unsigned)v < (unsigned)a.g.n) store_relaxed(&a.w.stamp[v], it);
+    }
+    for (long long i = tid; i < hubs; i += nt) store_relaxed(&a.w.stamp[a.w.reg_m[par][i]], it);
+  } else {
+    unsigned *dist = (unsigned *)a.state_i;
+    long long arcs = 0;
+    for (long long v = tid; v < a.g.n; v += nt) {
+      const unsigned d = dist[v];
+      if (d <= lowest) arcs += a.g.off[v + 1] - a.g.off[v];
+      else if (d != 0xFFFFFFFFu) store_relaxed(&dist[v], 0xFFFFFFFFu);
+    }
+    arcs = wave_sum_ll(arcs);
+    if (lane_id() == 0 && arcs) atomic_add_u64((unsigned long long *)&a.w.ctrl->aux.v[28], (unsigned long long)arcs);
+  }
+}
+// Arcs of the vertices that a run come back has not reached.
+SX_DEV unsigned long long cas_unexplored(const TravArgs &a) {
+  return (unsigned long long)a.g.m - load_relaxed((const unsigned long long *)&a.w.ctrl->aux.v[28]);
 }
 
 }  // namespace sx

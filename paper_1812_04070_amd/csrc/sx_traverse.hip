@@ -656,6 +656,8 @@ struct RunState {
   Params P;
   unsigned B = 0xFFFFFFFFu;     // delta-stepping bound (sequenced SSSP)
   unsigned dropped = 0;         // 1: buckets dropped for the rest of the run
+  int hold = 0;                 // the cascade is not entered before this iteration
+  unsigned casc = 0;            // cascade steps so far (batched runs)
 };
 
 struct LdsPolicy {
@@ -771,7 +773,7 @@ SX_DEV bool entry_done(Ctrl *C) {
 constexpr unsigned long long kCascadeMaxArcs = 1ull << 16;
 SX_DEV bool cascade_due(const TravArgs &a, const RunState &s, bool pulling, const Decision &d, const Totals &T,
                         unsigned nf_before) {
-  return a.cascade_after && s.it + 1 >= a.cascade_after && !pulling && !d.to_pull && !d.ballot && !s.dropped &&
+  return a.cascade_after && s.it + 1 >= a.cascade_after && s.it + 1 >= s.hold && !pulling && !d.to_pull && !d.ballot && !s.dropped &&
          T.mf <= kCascadeMaxArcs && T.nf <= nf_before + nf_before / 2 + 64u;
 }
 
@@ -799,14 +801,14 @@ SX_DEV void cascade_words(Ctrl *C, unsigned total, unsigned lowest) {
   for (int k = 0; k < 3; ++k) {
     store_relaxed(&C->aux.v[8 + k], k == 0 ? total : 0u);
     store_relaxed(&C->aux.v[12 + k], k == 0 ? lowest : 0xFFFFFFFFu);
-    store_relaxed(&C->aux.v[16 + k], 0u);
     store_relaxed(&C->aux.v[24 + k], 0u);
   }
+  store_relaxed((unsigned long long *)&C->aux.v[28], 0ull);
 }
 
 // The cascade over a team of workgroups, a step per barrier.  Returns
-// EXIT_DONE, EXIT_ERROR, or EXIT_SWITCH when a BFS goes back to its levels
-// (s.it: the level of the listed vertices).
+// EXIT_DONE, EXIT_ERROR, or EXIT_SWITCH when the run goes back to its phases
+// (s.it: their next iteration, whose lists a ballot scan makes).
 template <class Ops>
 SX_DEV int cascade_loop(const VGrid &vg, const TravArgs &a, GridBarrier &bar, LdsCas<Ops::kWeighted> &S,
                         RunState &s, const ViewRef &cur, const Totals &T) {
@@ -828,24 +830,25 @@ SX_DEV int cascade_loop(const VGrid &vg, const TravArgs &a, GridBarrier &bar, Ld
     __syncthreads();
   }
   if (lead) cascade_words(C, before, Ops::kWeighted ? 0u : (unsigned)s.it + 1u);
-  // stamps: every step's smallest distance is above the last one's, so no two
-  // steps of a run share one, also where a BFS comes back here
-  const unsigned from = (unsigned)s.it;
-  unsigned par = from & 1u;
+  unsigned par = (unsigned)s.it & 1u;
   if (!bar.sync()) return EXIT_ERROR;
   for (unsigned step = 0;; ++step) {
     if (t < 32) S.in[t] = load_relaxed(&C->aux.v[t]);
     cas_begin(S);
     __syncthreads();
     const unsigned now = step % 3, nxt = (step + 1) % 3;
-    const unsigned cnt = S.in[8 + now], lowest = S.in[12 + now], left = S.in[16 + now], hubs = S.in[24 + now];
+    const unsigned cnt = S.in[8 + now], lowest = S.in[12 + now], hubs = S.in[24 + now];
     if (cnt + hubs == 0) {
       if (!Ops::kWeighted) cas_levels<kBlock>(vg, a);
       return EXIT_DONE;
     }
-    if (!Ops::kWeighted && cnt > kCasMaxList && left == 0) {
-      if (lead) store_relaxed(&C->stats.v[6], lowest);
-      s.it = (int)lowest;
+    if (cas_outgrown(cnt, before)) {
+      s.it = Ops::kWeighted ? s.it + 2 : (int)lowest;
+      s.hold = s.it + kCasHold;
+      if (!Ops::kWeighted && lead) store_relaxed(&C->stats.v[6], lowest);
+      cas_way_back<Ops::kWeighted, kBlock>(vg, a, cnt, hubs, par, lowest, s.it);
+      if (!bar.sync()) return EXIT_ERROR;
+      if (!Ops::kWeighted) s.mu = cas_unexplored(a);
       return EXIT_SWITCH;
     }
     if (!Ops::kWeighted) window = cas_window(window, cnt, before, a.cascade_window);
@@ -855,7 +858,8 @@ SX_DEV int cascade_loop(const VGrid &vg, const TravArgs &a, GridBarrier &bar, Ld
       cas_clear(C, step, t);
       if (Ops::kWeighted && t == 4) atomic_add_u32(&C->stats.v[6], 1u);
     }
-    cascade_step<Ops::kWeighted, kBlock>(vg, a, S, cnt, hubs, B, par, nxt, (int)(0x40000000u | (from + step)));
+    // (a stamp of the run's own for each of its steps)
+    cascade_step<Ops::kWeighted, kBlock>(vg, a, S, cnt, hubs, B, par, nxt, (int)(0x40000000u | s.casc++));
     par ^= 1u;
     if (!bar.sync()) return EXIT_ERROR;
   }
@@ -920,6 +924,7 @@ SX_DEV int run_loop(const VGrid &vg, const TravArgs &a, GridBarrier &bar, LdsTra
             if (!bar.sync()) return EXIT_ERROR;
             T = make_view(vg, a, SLOT_SCAN, s.it & 1, lds, ref);
             if (!scan_fits(a, T)) return EXIT_ERROR;
+            s.ps.nf_prev = T.nf;
             rebuilt = true;
             continue;
           }
@@ -1054,8 +1059,9 @@ __global__ void __launch_bounds__(kBlock) k_pull_step(TravArgs a, int it) {
 // seq line: [0] phase [1] iteration [2,3] unexplored arcs [4] previous
 // frontier size [6,7] activated so far [8] t1 [9] t2 [10] pulling [11] 1: a
 // decision is due; 2: the scan lists what a marking step improved, whose count
-// no decision has seen [12] the push lists come from a ballot scan [13] the
-// delta-stepping bound (0: not set yet) [14] buckets dropped (pull steps)
+// no decision has seen; 3: the same of a run come back from the cascade [12] the push lists come from a ballot scan [13] the
+// delta-stepping bound (0: not set yet) [14] buckets dropped (pull steps) [15]
+// iteration before which the cascade is not entered; [16..19] the cascade's own
 SX_DEV void seq_store(Line &l, unsigned phase, const RunState &s, unsigned pulling, unsigned due,
                       unsigned rebuilt) {
   store_relaxed(&l.v[0], phase);
@@ -1070,6 +1076,7 @@ SX_DEV void seq_store(Line &l, unsigned phase, const RunState &s, unsigned pulli
   store_relaxed(&l.v[12], rebuilt);
   store_relaxed(&l.v[13], s.B);
   store_relaxed(&l.v[14], s.dropped);
+  store_relaxed(&l.v[15], (unsigned)s.hold);
 }
 
 // Hand the run over to k_cascade's launches.
@@ -1118,6 +1125,7 @@ SX_DEV bool seq_body(const TravArgs &a, unsigned L, LdsTrav &lds, LdsPolicy &pol
   unsigned rebuilt = in[12];
   s.B = in[13] ? in[13] : (a.P.delta && a.P.delta_after == 0 ? a.P.delta : 0xFFFFFFFFu);
   s.dropped = in[14];
+  s.hold = (int)in[15];
   if (phase >= SEQ_DONE) {
     if (lead) seq_store(out, phase, s, pulling, 0, rebuilt);
     return false;
@@ -1202,8 +1210,8 @@ SX_DEV bool seq_body(const TravArgs &a, unsigned L, LdsTrav &lds, LdsPolicy &pol
         if (rebuilt && !scan_fits(a, T)) break;
       }
       if (due == 2) {
-        // after a marking step: the end, and the counts that a later decision
-        // goes by (the direction is not open, see mark)
+        // after a marking step or the cascade: the end, and the counts that a
+        // later decision goes by (the direction is not open, see mark)
         if (T.nf == 0 || s.it >= a.P.max_iters) {
           ends();
           return true;
@@ -1224,10 +1232,11 @@ SX_DEV bool seq_body(const TravArgs &a, unsigned L, LdsTrav &lds, LdsPolicy &pol
       }
       break;
     case PH_BALLOT:
+      if (kCascade && Ops::kVote && due == 3) s.mu = cas_unexplored(a);
       // rebuild the lists of it+1, then push them
       ballot_next(vg, a, s.P, ops, it, lds);
       ++s.it;
-      if (lead) seq_store(out, PH_PUSH, s, 0, due == 2 ? 2 : 0, 1);
+      if (lead) seq_store(out, PH_PUSH, s, 0, due >= 2 ? 2 : 0, 1);
       break;
     case PH_PULL_SCAN:
       if (lead) atomic_add_u32(&C->stats.v[6], 1u);
