@@ -117,6 +117,15 @@ SX_DEV unsigned cas_window(unsigned window, unsigned cnt, unsigned before, unsig
   return window * 2 < most ? window * 2 : most;
 }
 
+// Eight times the mean weight, of 512 arcs spread over the graph: an SSSP
+// step's window (a whole wavefront; the same in all).
+SX_DEV unsigned cas_mean8(const TravArgs &a) {
+  long long sum = 0;
+  for (int k = 0; k < 8; ++k) sum += a.g.w[a.g.m * (lane_id() * 8 + k) / 512];
+  const unsigned long long mean8 = (unsigned long long)wave_sum_ll(sum) / 64;
+  return mean8 < 1 ? 1u : mean8 > 0x7FFFFFFFull ? 0x7FFFFFFFu : (unsigned)mean8;
+}
+
 // Whether a list is the phases' business: long, or many times the one before
 // (meshes' lists grow by half a step at most; a blob's first vertices overflow
 // one workgroup's queue, and the next step would walk all of it unsynchronised).

@@ -920,9 +920,9 @@ static bool engine_schedules(const sx_policy &pol) {
 // over after 8 levels of a frontier that stays light (2^16 arcs) and does not
 // grow by half, an SSSP with buckets after 16 iterations (64^2 grid BFS 1.86 ->
 // 0.36 ms; random and R-MAT graphs of 3-6 arcs per vertex reach the threshold
-// in their last, light levels if at all).  The window: 64 levels, or the
-// caller's bucket width; the automatic width of 40 mean weights is for phases
-// whose fixed cost is a launch, a cascade's best is 8.
+// in their last, light levels if at all).  The window: 64 levels, or 8 mean
+// weights (a caller's narrower bucket width is kept): the automatic width of 40
+// is for phases whose fixed cost is a launch.
 static const int kCascadeGrid = 1024;
 // launches per batch where the cascade may take over: one takes 20-80 us, so
 // the host keeps ahead with few, and few run after the end

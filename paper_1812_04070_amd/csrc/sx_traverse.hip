@@ -816,19 +816,9 @@ SX_DEV int cascade_loop(const VGrid &vg, const TravArgs &a, GridBarrier &bar, Ld
   const int t = threadIdx.x;
   const bool lead = vg.bid == 0 && t == 0;
   unsigned before = cascade_list(vg, a, s, cur, T), window = 1u;
-  if constexpr (Ops::kWeighted) {
-    // a window of 8 mean weights, of the same 512 arcs in every workgroup (the
-    // smallest listed distance is not kept without buckets: 0 makes the first
-    // step's window end low, and the step then carries what lies beyond it)
-    if (t == 0) S.edges = 0ull;
-    __syncthreads();
-    const long long sum = wave_sum_ll((long long)a.g.w[a.g.m * t / kBlock]);
-    if (lane_id() == 0) atomicAdd(&S.edges, (unsigned long long)sum);
-    __syncthreads();
-    const unsigned long long mean8 = S.edges / (kBlock / 8);
-    window = mean8 < 1 ? 1u : mean8 > 0x7FFFFFFFull ? 0x7FFFFFFFu : (unsigned)mean8;
-    __syncthreads();
-  }
+  // (the smallest listed distance is not kept without buckets: 0 makes the
+  // first step's window end low, and the step then carries what lies beyond it)
+  if constexpr (Ops::kWeighted) window = cas_mean8(a);
   if (lead) cascade_words(C, before, Ops::kWeighted ? 0u : (unsigned)s.it + 1u);
   unsigned par = (unsigned)s.it & 1u;
   if (!bar.sync()) return EXIT_ERROR;
@@ -1085,10 +1075,20 @@ SX_DEV void cascade_enter(const VGrid &vg, const TravArgs &a, const RunState &s,
                           const Totals &T, Line &out) {
   Ctrl *C = a.w.ctrl;
   const unsigned total = cascade_list(vg, a, s, cur, T);
-  if (vg.bid == 0 && threadIdx.x == 0) {
+  if (vg.bid != 0 || wave_in_wg() != 0) return;
+  unsigned window = Ops::kVote ? 1u : a.cascade_window;
+  if constexpr (Ops::kWeighted) {
+    // A caller's bucket width is for phases whose fixed cost is a launch; as a
+    // window, one beyond 8 mean weights only repeats relaxations (1024^2 grid
+    // of weights 1..1000: width 5,000 4.8 ms, 2^20 as its own window 70, the
+    // phases 42; so capped 4.7).
+    const unsigned most = cas_mean8(a);
+    if (a.P.delta_after == 0 && window > most) window = most;
+  }
+  if (threadIdx.x == 0) {
     cascade_words(C, total, Ops::kVote ? (unsigned)s.it + 1u : load_relaxed(&C->aux.v[(s.it + 1) % 3]));
     seq_store(out, PH_CASCADE, s, 0, 0, 0);
-    store_relaxed(&out.v[16], Ops::kVote ? 1u : a.cascade_window);
+    store_relaxed(&out.v[16], window);
     store_relaxed(&out.v[17], total);
     store_relaxed(&out.v[18], 0u);
     store_relaxed(&out.v[19], (unsigned)s.it & 1u);
