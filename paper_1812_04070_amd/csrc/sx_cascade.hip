@@ -33,6 +33,7 @@ __global__ void __launch_bounds__(kCasBlock) k_cascade(TravArgs a, unsigned L) {
     // the run is over; BFS counts its levels (the depths reached)
     if (!kWeighted) cas_levels<kCasBlock>(hw_grid(), a);
     if (blockIdx.x == 0 && t < 32) store_relaxed(&out.v[t], t == 0 ? (unsigned)SEQ_DONE : in[t]);
+    if (blockIdx.x == 0 && t == 32) store_relaxed(&C->stats.v[12], L + 1u);
     return;
   }
   // back to the phases: a ballot scan after iteration it - 1, then iteration `it`

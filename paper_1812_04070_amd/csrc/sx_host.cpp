@@ -126,6 +126,9 @@ struct sx_graph {
   // (0: none yet): the next run enqueues that many plus kSeqHintMargin in its
   // first batch instead of 16, so few launches run after the end
   int seq_hint[3] = {0, 0, 0};
+  // if the cascade took that run on: seq_hint counts the launches before it,
+  // this one those from there to the end (0: it did not)
+  int seq_cascaded[3] = {0, 0, 0};
   // the call in progress on a renumbered graph: the caller's array, and
   // whether the mapping of the result into it has been enqueued behind the
   // run's last kernel (map_back)
@@ -705,22 +708,26 @@ static sx_status map_back(sx_graph *G, hipStream_t st, const unsigned *phase = n
 // (about 2 us).  On return `*fin` points at the pinned copy of the control
 // block taken after the batch that ended the run.  `ends_first`: the first
 // batch is expected to end the run, so the result's mapping and ev1 go behind
-// it; *ended_first says whether it did (then both are done).
-template <class Launch>
-static sx_status seq_drive(sx_graph *G, hipStream_t st, int first, int maxb, unsigned limit,
+// it; *ended_first says whether it did (then both are done).  `second` > 0:
+// launches of the second batch, which is expected to end the run and so is
+// checked before more are enqueued too.  most(): the largest batch by now.
+template <class Most, class Launch>
+static sx_status seq_drive(sx_graph *G, hipStream_t st, int first, Most most, unsigned limit,
                            Launch launch, int &launches, const Ctrl **fin, unsigned *fin_phase = nullptr,
-                           bool ends_first = false, bool *ended_first = nullptr) {
+                           bool ends_first = false, bool *ended_first = nullptr, int second = 0) {
   struct Pend {
     Ctrl *h;
     hipEvent_t ev;
     unsigned L;
   } pend[2] = {{G->h_ctrl, G->evb[0], 0u}, {G->h_ctrl2, G->evb[1], 0u}};
   unsigned L = 0;
-  int batch = first;
-  auto enqueue = [&](Pend &p) -> sx_status {
+  int last = first;
+  auto enqueue = [&](Pend &p, int batch) -> sx_status {
+    const bool opening = L == 0;
     for (int k = 0; k < batch; ++k) HIP_TRY(launch(L++));
     launches += batch;
-    if (ends_first && L == (unsigned)batch) {
+    last = batch;
+    if (ends_first && opening) {
       sx_status m = map_back(G, st, &G->w.ctrl->seq[L & 1].v[0], SEQ_DONE);
       if (m != SX_OK) return m;
       HIP_TRY(hipEventRecord(G->ev1, st));
@@ -728,13 +735,13 @@ static sx_status seq_drive(sx_graph *G, hipStream_t st, int first, int maxb, uns
     HIP_TRY(hipMemcpyAsync(p.h, G->w.ctrl, offsetof(Ctrl, flags), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipEventRecord(p.ev, st));
     p.L = L;
-    batch = std::min(batch * 2, maxb);
     return SX_OK;
   };
-  sx_status s = enqueue(pend[0]);
+  auto next = [&]() { return std::min(last * 2, most()); };
+  sx_status s = enqueue(pend[0], first);
   if (s != SX_OK) return s;
   int cur = 0;
-  bool piped = false;
+  bool piped = false, opening = true;
   for (;;) {
     Pend &p = pend[cur];
     HIP_TRY(hipEventSynchronize(p.ev));
@@ -745,18 +752,25 @@ static sx_status seq_drive(sx_graph *G, hipStream_t st, int first, int maxb, uns
     if (ph == SEQ_LIMIT) return fail(SX_EHIP, "iteration limit reached (engine bug)");
     if (ph >= SEQ_DONE) {
       *fin = p.h;
-      if (ended_first) *ended_first = ends_first && !piped;
+      if (ended_first) *ended_first = ends_first && opening;
       return SX_OK;
     }
     G->mapped = false;   // not over: nothing was written
     if (L > limit) return fail(SX_EHIP, "run did not converge");
+    opening = false;
+    if (second > 0) {
+      s = enqueue(p, second);
+      if (s != SX_OK) return s;
+      second = 0;
+      continue;
+    }
     if (!piped) {
-      // second and third batch: from here on one batch stays in flight
-      s = enqueue(pend[cur ^ 1]);
+      // two batches: from here on one stays in flight
+      s = enqueue(pend[cur ^ 1], next());
       if (s != SX_OK) return s;
       piped = true;
     }
-    s = enqueue(p);
+    s = enqueue(p, next());
     if (s != SX_OK) return s;
     cur ^= 1;
   }
@@ -924,9 +938,11 @@ static bool engine_schedules(const sx_policy &pol) {
 // weights (a caller's narrower bucket width is kept): the automatic width of 40
 // is for phases whose fixed cost is a launch.
 static const int kCascadeGrid = 1024;
-// launches per batch where the cascade may take over: one takes 20-80 us, so
-// the host keeps ahead with few, and few run after the end
-static const int kCascadeBatch = 16;
+// cascade launches per batch: one takes 20-80 us, so the host keeps ahead with
+// few, and few run after the end or a way back to the phases (one of those
+// costs 5 us); and the most launches of a cascade that are enqueued in one batch
+// where the last run needed no more
+static const int kCascadeBatch = 6, kCascadeEnds = 16;
 
 // max_it > 0: stop the one-phase arrangement after that many iterations and
 // note where the next iteration's lists are (sx_run_iterations).
@@ -999,20 +1015,26 @@ static sx_status run_traversal(sx_program *p, sx_graph *G, int src, void *d_out,
     // workgroups of the wide kernel): size the first batch by the last run of
     // this algorithm on this graph (another source: a different count; too
     // few launches only cost one host round trip before the next batch)
+    // (a run that the cascade took on: its launches up to there)
     int &hint = G->seq_hint[algo];
+    int &cascaded = G->seq_cascaded[algo];
     const int first = hint > 0 ? std::min(hint + kSeqHintMargin, 64) : 16;
     unsigned phase = PH_PUSH;
     bool timed = false;
     sx_status s = seq_drive(
-        G, st, first, a.cascade_after ? kCascadeBatch : 64, (unsigned)(8 * (long long)G->g.n + 1024),
+        G, st, first, [&] { return !a.cascade_after ? 64 : phase == PH_CASCADE ? kCascadeBatch : 16; },
+        (unsigned)(8 * (long long)G->g.n + 1024),
         [&](unsigned L) {
           return phase == PH_CASCADE ? cascade_launch(a, algo == ALG_SSSP, L, kCascadeGrid, st)
                                      : trav_launch(seq_kind, algo, a, (int)L, 0, grid, st);
         },
-        launches, &fin, &phase, hint > 0, &timed);
+        launches, &fin, &phase, hint > 0 && cascaded == 0, &timed,
+        cascaded > 0 && cascaded <= kCascadeEnds ? cascaded + kSeqHintMargin : 0);
     if (s != SX_OK) return s;
-    // Ctrl::stats word 12: the index + 1 of the launch that ended the run
-    hint = (int)fin->stats.v[12];
+    // Ctrl::stats word 12: the index + 1 of the launch that ended the run, 13:
+    // of the one that handed it to the cascade (0: none did)
+    hint = (int)(fin->stats.v[13] ? fin->stats.v[13] : fin->stats.v[12]);
+    cascaded = (int)fin->stats.v[12] - hint;
     if (!timed) {
       s = map_back(G, st);
       if (s != SX_OK) return s;
@@ -1218,7 +1240,7 @@ static sx_status run_kcore(sx_program *p, sx_graph *G, void *d_out, hipStream_t 
     const Ctrl *fin = G->h_ctrl;
     unsigned ph = 0;
     sx_status s = seq_drive(
-        G, st, 16, 16, (unsigned)(16 * (long long)G->g.n + 1024),
+        G, st, 16, [] { return 16; }, (unsigned)(16 * (long long)G->g.n + 1024),
         [&](unsigned L) { return kcore_seq_launch(a, L, grid, st, false); }, launches, &fin, &ph);
     if (s != SX_OK) return s;
     if (ph == KP_TAIL) {

@@ -1092,8 +1092,9 @@ SX_DEV void cascade_enter(const VGrid &vg, const TravArgs &a, const RunState &s,
     store_relaxed(&out.v[17], total);
     store_relaxed(&out.v[18], 0u);
     store_relaxed(&out.v[19], (unsigned)s.it & 1u);
-    // the next run's first batch of launches ends here
-    store_relaxed(&C->stats.v[12], L + 1u);
+    // the next run's first batch of launches ends here (a run that comes back
+    // may enter again: the first time counts)
+    if (load_relaxed(&C->stats.v[13]) == 0u) store_relaxed(&C->stats.v[13], L + 1u);
   }
 }
 

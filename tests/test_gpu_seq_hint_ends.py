@@ -62,3 +62,27 @@ def test_near_run_after_far_run_and_back(engine, reorder):
             out, _ = run(engine, h, algo, s, SEQ, dg=dg)
             np.testing.assert_array_equal(out, oracle_fn(h, s))
     dg.close()
+
+
+def test_repeated_cascade_run_enqueues_what_it_needs(engine):
+    """Runs that the cascade takes on near their end: the launches before it and
+    those from it on are sized by the last run's, so that a repeated run
+    enqueues about as many as the phases alone do (the margin of two once more,
+    the step that finds the list empty, and a few for windows cut short)."""
+    r = np.random.default_rng(3)
+    n = 1 << 21
+    g = gen.from_edges(n, r.integers(0, n, (2 * n, 2)), r.integers(1, 65, 2 * n))
+    s = gen.max_degree_vertex(g)
+    ref = oracle.bfs_g(g, s)
+    for reorder in (False, True):
+        dg = engine.load(g, reorder=reorder)
+        launches = {}
+        for name, pol in (("phases", SEQ), ("cascade", None)):
+            for rep in range(4):
+                announce(f"cascade tail {name} reorder={reorder} rep {rep}")
+                out, st = run(engine, g, sx.SX_BFS, s, pol, dg=dg)
+                np.testing.assert_array_equal(out, ref)
+                launches[name, rep] = st["launches"]
+        print(f"[seq-hint] cascade tail launches {launches}", flush=True)
+        assert all(launches["cascade", k] <= launches["phases", 3] + 8 for k in (1, 2, 3)), launches
+        dg.close()
