@@ -1149,9 +1149,9 @@ static sx_status run_traversal(sx_program *p, sx_graph *G, int src, void *d_out,
 // be.  us a run, phases -> one workgroup: BFS R-MAT s8 / s10 / s12 109 -> 37,
 // 117 -> 46, 116 -> 81, from 2^18 arcs on it loses (s14 137 -> 258); an SSSP
 // relaxes every arc two or three times, s10 192 -> 92, s12 (97 K arcs) 220 ->
-// 222 with the caller's numbering; grids, whose iterations are many and light,
-// as far as the LDS goes: side 155 (24,025 vertices) BFS 535 -> 343, SSSP
-// 4,470 -> 1,980.
+// 222 with the caller's numbering; sparse graphs as far as the LDS goes: grid
+// of side 155 (24,025 vertices) BFS 535 -> 343, SSSP 4,580 -> 1,216; stars and
+// random graphs of 16,000 to 24,000 vertices SSSP 98-367 -> 75-228.
 static bool small_run(const sx_program *p, const sx_graph *G) {
   if (!engine_schedules(p->pol) || p->pol.policy != SX_POLICY_HEURISTIC || G->g.n > kSmallN) return false;
   if (p->ap.algo == SX_BFS) return G->g.m <= (1ll << 17);

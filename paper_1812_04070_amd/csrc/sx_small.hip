@@ -10,8 +10,11 @@
 // An iteration expands the listed vertices from the distances they had when
 // the list was made, so the iterations are the synchronous rounds of the
 // frontier form (Active, Compute and Combine as in sx_traverse.hip), whatever
-// the order of the updates within one.  Rows go to 8 lanes, a wavefront or the
-// workgroup by length.
+// the order of the updates within one.  Rows go to 2 or 8 lanes, a wavefront or
+// the workgroup by length.  Two lanes hold the short rows of graphs of at most 4
+// arcs per vertex: with 8, a list of most of 20,000 vertices took 160 passes of
+// the workgroup (star of 20,000 SSSP 196 -> 101 us, the phases 103; a
+// random graph of 24,000 and 3.3 447 -> 228, the phases 364).
 //
 // Bound by one CU's rate of row reads and LDS atomics once the graph is large:
 // the limits (sx_host.cpp) lie where the grid's phases catch up.
@@ -24,7 +27,7 @@ constexpr int kSmIlp = 4;                // arcs of a lane in flight
 constexpr int kSmBlock = 1024, kSmWaves = kSmBlock / 64;
 constexpr int kSmWaveRow = 64;           // arcs from which a wavefront takes a row
 constexpr int kSmGroupRow = 2048;        // and the workgroup
-constexpr int kSmLong = 1024, kSmHuge = 64;   // such rows listed per iteration (more: 8 lanes)
+constexpr int kSmLong = 1024, kSmHuge = 64;   // such rows listed per iteration (the others stay)
 
 struct LdsSmall {
   unsigned dist[kSmallN];
@@ -36,7 +39,7 @@ struct LdsSmall {
   unsigned long long edges;
 };
 
-template <bool kWeighted>
+template <bool kWeighted, int kLanes>
 __global__ void __launch_bounds__(kSmBlock) k_small(TravArgs a, int *out, const int *inv) {
   __shared__ LdsSmall S;
   const int n = a.g.n, t = threadIdx.x, lane = lane_id(), wv = wave_in_wg();
@@ -114,21 +117,21 @@ __global__ void __launch_bounds__(kSmBlock) k_small(TravArgs a, int *out, const 
   while (lo < hi) {
     ++it;
     if (t == 0) ents += hi - lo;
-    for (unsigned i = lo + (unsigned)t / 8u; i < hi; i += kSmBlock / 8) {
+    for (unsigned i = lo + (unsigned)t / kLanes; i < hi; i += kSmBlock / kLanes) {
       const int v = S.list[i];
       const int beg = off[v], end = off[v + 1];
       const unsigned d = kWeighted ? at_list[v] : it - 1;
       bool own = true;
       if (end - beg >= kSmWaveRow) {
-        // lane 0 of the eight lists it; all follow
+        // the first of the lanes lists it; all follow
         unsigned p = 0;
         const bool huge = end - beg >= kSmGroupRow;
-        if (lane % 8 == 0) p = atomicAdd(huge ? &S.gn : &S.wn, 1u);
-        p = __shfl(p, lane & ~7);
+        if (lane % kLanes == 0) p = atomicAdd(huge ? &S.gn : &S.wn, 1u);
+        p = __shfl(p, lane & ~(kLanes - 1));
         own = p >= (unsigned)(huge ? kSmHuge : kSmLong);
-        if (!own && lane % 8 == 0) (huge ? S.grow : S.wrow)[p] = (unsigned short)v;
+        if (!own && lane % kLanes == 0) (huge ? S.grow : S.wrow)[p] = (unsigned short)v;
       }
-      if (own) walk(beg, end, d, lane % 8, 8);
+      if (own) walk(beg, end, d, lane % kLanes, kLanes);
     }
     __syncthreads();
     const unsigned wn = S.wn < (unsigned)kSmLong ? S.wn : (unsigned)kSmLong;
@@ -188,8 +191,10 @@ __global__ void __launch_bounds__(kSmBlock) k_small(TravArgs a, int *out, const 
 }
 
 hipError_t small_launch(const TravArgs &a, bool weighted, int *out, const int *inv, hipStream_t s) {
-  if (weighted) hipLaunchKernelGGL(k_small<true>, dim3(1), dim3(kSmBlock), 0, s, a, out, inv);
-  else hipLaunchKernelGGL(k_small<false>, dim3(1), dim3(kSmBlock), 0, s, a, out, inv);
+  const bool sparse = a.g.m <= 4ll * a.g.n;
+  const auto k = weighted ? (sparse ? k_small<true, 2> : k_small<true, 8>)
+                          : (sparse ? k_small<false, 2> : k_small<false, 8>);
+  hipLaunchKernelGGL(k, dim3(1), dim3(kSmBlock), 0, s, a, out, inv);
   return hipGetLastError();
 }
 
