@@ -982,7 +982,7 @@ static sx_status run_traversal(sx_program *p, sx_graph *G, int src, void *d_out,
     // 4-6 arcs per vertex lost 5-13 % to buckets from the first iteration)
     a.P.delta_after = 64;
   }
-  if (sequenced && engine_schedules(p->pol) && G->g.m < 8ll * G->g.n && G->g.m >= 4) {
+  if (sequenced && engine_schedules(p->pol) && cascade_graph(G->g)) {
     if (algo == ALG_BFS) {
       a.cascade_after = kCascadeAfterBfs;
       a.cascade_window = kCascadeLevels;
@@ -1649,7 +1649,11 @@ extern "C" sx_status sx_run_batch(sx_ctx *ctx, const sx_query *q, int32_t nq, co
   if (cfg) c = *cfg;
   else if (ctx->tuned.team_wgs > 0) c = ctx->tuned;
   int per = 0;
-  HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, batch_kernel(), kBlock, 0));
+  // (bin thresholds a configuration sets are the level phases' only)
+  bool cascade = false;
+  if (!pol || engine_schedules(*pol))
+    for (int i = 0; i < nq; ++i) cascade = cascade || cascade_graph(q[i].g->g);
+  HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, batch_kernel(cascade), kBlock, 0));
   const int grid = std::max(1, std::min(per * ctx->cus, kMaxGrid));
   if (c.team_wgs < 1 || c.team_wgs > kMaxTeam) return fail(SX_EINVAL, "team_wgs must be in 1..%d", kMaxTeam);
   const int team = std::min(c.team_wgs, grid);
@@ -1673,8 +1677,7 @@ extern "C" sx_status sx_run_batch(sx_ctx *ctx, const sx_query *q, int32_t nq, co
   b.nq = nq;
   b.nteams = nteams;
   b.team = team;
-  // (bin thresholds a configuration sets are the level phases' only)
-  b.cascade = !pol || engine_schedules(*pol) ? 1 : 0;
+  b.cascade = cascade ? 1 : 0;
   // device-side query table, order (largest expected time first), stats
   std::vector<BatchQuery> hq((size_t)nq);
   std::vector<std::pair<double, int>> key((size_t)nq);
@@ -2050,7 +2053,7 @@ extern "C" sx_status sx_kernel_info_get(sx_ctx *ctx, const char *name, sx_kernel
       {"pagerank_until_stable", pagerank_kernel(true), true, kPagerankBlock},
       {"pagerank_push_tail", pagerank_push_kernel(), true},
       {"bp_fused", bp_kernel(), true, kBpBlock},
-      {"batch", batch_kernel(), true},
+      {"batch", batch_kernel(true), true},
   };
   for (const Named &t : table) {
     if (strcmp(t.name, name) != 0) continue;

@@ -33,7 +33,7 @@ hipError_t weight_sum(const unsigned *w, long long m, unsigned long long *out, h
 enum : unsigned { PH_PUSH = 0, PH_BALLOT = 1, PH_PULL_SCAN = 2, PH_PULL = 3, PH_CASCADE = 4,
                   SEQ_DONE = 6, SEQ_ERROR = 7, SEQ_LIMIT = 8 };
 hipError_t cascade_launch(const TravArgs &a, bool weighted, unsigned L, int grid, hipStream_t s);
-const void *batch_kernel();
+const void *batch_kernel(bool cascade);
 
 // components by hooking; *launches = kernels enqueued
 hipError_t wcc_launch(const WccArgs &a, int cus, hipStream_t s, int *launches);

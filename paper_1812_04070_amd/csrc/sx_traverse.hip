@@ -657,7 +657,7 @@ struct RunState {
   unsigned B = 0xFFFFFFFFu;     // delta-stepping bound (sequenced SSSP)
   unsigned dropped = 0;         // 1: buckets dropped for the rest of the run
   int hold = 0;                 // the cascade is not entered before this iteration
-  unsigned casc = 0;            // cascade steps so far (batched runs)
+  unsigned casc = 0, listed = 0;   // cascade steps so far, length of its first list (batched runs)
 };
 
 struct LdsPolicy {
@@ -769,12 +769,16 @@ SX_DEV bool entry_done(Ctrl *C) {
 
 // ----------------------------------------------------------- cascade ---
 // Whether a run goes over to the cascade after iteration s.it: it has run for
-// a while and its frontier is light and does not grow: a high diameter.
-constexpr unsigned long long kCascadeMaxArcs = 1ull << 16;
-SX_DEV bool cascade_due(const TravArgs &a, const RunState &s, bool pulling, const Decision &d, const Totals &T,
+// a while and its frontier is light and does not grow: a high diameter.  Light
+// for a team of few workgroups is less (16 SSSP queries on a random graph of
+// 200,000 vertices and 7 arcs each by teams of 4: in phases alone 7.85 ms, from
+// 2^16 arcs on in the cascade 8.56, by this rule 8.40; 2^9 arcs a workgroup the
+// same).
+constexpr unsigned long long kCascadeMaxArcs = 1ull << 16, kCascadeWgArcs = 1ull << 11;
+SX_DEV bool cascade_due(const VGrid &vg, const TravArgs &a, const RunState &s, bool pulling, const Decision &d, const Totals &T,
                         unsigned nf_before) {
   return a.cascade_after && s.it + 1 >= a.cascade_after && s.it + 1 >= s.hold && !pulling && !d.to_pull && !d.ballot && !s.dropped &&
-         T.mf <= kCascadeMaxArcs && T.nf <= nf_before + nf_before / 2 + 64u;
+         T.mf <= kCascadeMaxArcs && T.mf <= vg.nb * kCascadeWgArcs && T.nf <= nf_before + nf_before / 2 + 64u;
 }
 
 // The lists of iteration it + 1 (view `cur`) as one array, in the buffer of
@@ -806,16 +810,17 @@ SX_DEV void cascade_words(Ctrl *C, unsigned total, unsigned lowest) {
   store_relaxed((unsigned long long *)&C->aux.v[28], 0ull);
 }
 
-// The cascade over a team of workgroups, a step per barrier.  Returns
+// The cascade over a team of workgroups, a step per barrier, from the s.listed
+// vertices that cascade_list listed.  Returns
 // EXIT_DONE, EXIT_ERROR, or EXIT_SWITCH when the run goes back to its phases
 // (s.it: their next iteration, whose lists a ballot scan makes).
 template <class Ops>
 SX_DEV int cascade_loop(const VGrid &vg, const TravArgs &a, GridBarrier &bar, LdsCas<Ops::kWeighted> &S,
-                        RunState &s, const ViewRef &cur, const Totals &T) {
+                        RunState &s) {
   Ctrl *C = a.w.ctrl;
   const int t = threadIdx.x;
   const bool lead = vg.bid == 0 && t == 0;
-  unsigned before = cascade_list(vg, a, s, cur, T), window = 1u;
+  unsigned before = s.listed, window = 1u;
   // (the smallest listed distance is not kept without buckets: 0 makes the
   // first step's window end low, and the step then carries what lies beyond it)
   if constexpr (Ops::kWeighted) window = cas_mean8(a);
@@ -835,6 +840,7 @@ SX_DEV int cascade_loop(const VGrid &vg, const TravArgs &a, GridBarrier &bar, Ld
     if (cas_outgrown(cnt, before)) {
       s.it = Ops::kWeighted ? s.it + 2 : (int)lowest;
       s.hold = s.it + kCasHold;
+      s.ps.nf_prev = cnt;
       if (!Ops::kWeighted && lead) store_relaxed(&C->stats.v[6], lowest);
       cas_way_back<Ops::kWeighted, kBlock>(vg, a, cnt, hubs, par, lowest, s.it);
       if (!bar.sync()) return EXIT_ERROR;
@@ -862,10 +868,11 @@ SX_DEV int cascade_loop(const VGrid &vg, const TravArgs &a, GridBarrier &bar, Ld
 // (EXIT_SWITCH) so that the host launches the other kernel; kDir 2: both
 // directions, switching in place (all fusion and the batched kernel).
 // Returns the exit reason.
-// `cas` (the batched kernel): LDS for a run that goes over to the cascade.
-template <class Ops, int kDir, bool kDedup = true, class Cas = int>
+// kCascade (batches with sparse graphs): the loop is left for the cascade
+// (EXIT_CASCADE, its list made).
+template <class Ops, int kDir, bool kDedup = true, bool kCascade = false>
 SX_DEV int run_loop(const VGrid &vg, const TravArgs &a, GridBarrier &bar, LdsTrav &lds,
-                    LdsPolicy &pol, RunState &s, bool &pulling, bool &rebuilt, Cas *cas = nullptr) {
+                    LdsPolicy &pol, RunState &s, bool &pulling, bool &rebuilt) {
   constexpr bool both = kDir == 2;
   Ctrl *C = a.w.ctrl;
   ViewRef ref;
@@ -904,19 +911,10 @@ SX_DEV int run_loop(const VGrid &vg, const TravArgs &a, GridBarrier &bar, LdsTra
         Decision d = decide<Ops>(a, s, false, T, &pol, vg.bid == 0);
         rebuilt = false;
         if (d.done) { ++s.it; return s.it >= a.P.max_iters ? EXIT_LIMIT : EXIT_DONE; }
-        if constexpr (!std::is_same<Cas, int>::value) {
-          if (cascade_due(a, s, pulling, d, T, nf_before)) {
-            const int r = cascade_loop<Ops>(vg, a, bar, *cas, s, ref, T);
-            if (r != EXIT_SWITCH) return r;
-            // a long frontier: its lists from the depths, then level by level
-            Ops at = make_ops<Ops>(a, s.it - 1);
-            ballot_next(vg, a, s.P, at, s.it - 1, lds);
-            if (!bar.sync()) return EXIT_ERROR;
-            T = make_view(vg, a, SLOT_SCAN, s.it & 1, lds, ref);
-            if (!scan_fits(a, T)) return EXIT_ERROR;
-            s.ps.nf_prev = T.nf;
-            rebuilt = true;
-            continue;
+        if constexpr (kCascade) {
+          if (cascade_due(vg, a, s, pulling, d, T, nf_before)) {
+            s.listed = cascade_list(vg, a, s, ref, T);
+            return EXIT_CASCADE;
           }
         }
         if (d.to_pull) {
@@ -1183,7 +1181,7 @@ SX_DEV bool seq_body(const TravArgs &a, unsigned L, LdsTrav &lds, LdsPolicy &pol
       }
     }
     if constexpr (kCascade) {
-      if (cascade_due(a, s, pulling != 0, d, T, nf_before)) {
+      if (cascade_due(vg, a, s, pulling != 0, d, T, nf_before)) {
         cascade_enter<Ops>(vg, a, s, L, ref, T, out);
         return true;
       }
@@ -1366,9 +1364,10 @@ __global__ void k_trav_init(TravArgs a, int algo, unsigned long long mu0, unsign
 // directions in one loop, switching in place -- synchronised by a barrier
 // over the team only, then takes the next.  Teams never wait for each other,
 // so a 6-level R-MAT query and a 4,000-level grid query overlap.
-template <class Ops>
+template <class Ops, class Cas>
 SX_DEV bool batch_query(const VGrid &vg, const TravArgs &a, GridBarrier &bar, LdsTrav &lds,
-                        LdsPolicy &pol, LdsCas<Ops::kWeighted> &cas, unsigned long long mu0) {
+                        LdsPolicy &pol, Cas *cas, unsigned long long mu0) {
+  constexpr bool cascade = !std::is_same<Cas, int>::value;
   RunState s;
   s.it = 0;
   s.mu = mu0;
@@ -1376,7 +1375,25 @@ SX_DEV bool batch_query(const VGrid &vg, const TravArgs &a, GridBarrier &bar, Ld
   s.ps.reached = 0;
   s.P = a.P;
   bool pulling = a.P.direction == 2, rebuilt = false;
-  const int r = run_loop<Ops, 2, false>(vg, a, bar, lds, pol, s, pulling, rebuilt, &cas);
+  int r;
+  for (;;) {
+    r = run_loop<Ops, 2, false, cascade>(vg, a, bar, lds, pol, s, pulling, rebuilt);
+    if constexpr (cascade) {
+      // (beside the loop of the phases, not in it: fewer registers spilled there)
+      if (r == EXIT_CASCADE) {
+        r = cascade_loop<Ops>(vg, a, bar, *cas, s);
+        if (r == EXIT_SWITCH) {
+          // back to the phases: their lists by a scan
+          Ops at = make_ops<Ops>(a, s.it - 1);
+          ballot_next(vg, a, s.P, at, s.it - 1, lds);
+          rebuilt = true;
+          if (bar.sync()) continue;
+          r = EXIT_ERROR;
+        }
+      }
+    }
+    break;
+  }
   finish(vg, a.w.ctrl, r, s, false);
   if (r == EXIT_ERROR) return false;
   return bar.sync();
@@ -1384,10 +1401,15 @@ SX_DEV bool batch_query(const VGrid &vg, const TravArgs &a, GridBarrier &bar, Ld
 
 // Four wavefronts per SIMD (128 VGPRs, spilling): two workgroups per CU, so
 // twice the teams run at once (256 queries over 64 graphs: 609 -> 561 ms).
+// kCascade: some query's graph is sparse enough for the cascade.  Batches of
+// dense graphs run without its code, which costs registers that every phase has
+// to spill (64 SSSP queries on R-MAT s12 / s15 / s17: with it inside the phases'
+// loop, 316 registers spilled, 2.65 / 5.39 / 13.5 ms; without, 139 spilled, 2.60 /
+// 4.86 / 11.9).  With it, beside that loop, 174 are spilled.
+template <bool kCascade>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) k_batch(BatchArgs b) {
   __shared__ LdsTrav lds;
   __shared__ LdsPolicy pol;
-  __shared__ union { LdsCas<true> sssp; LdsCas<false> bfs; } cas;
   const unsigned team = blockIdx.x / (unsigned)b.team;
   const VGrid vg{blockIdx.x % (unsigned)b.team, (unsigned)b.team};
   if (team >= (unsigned)b.nteams) return;
@@ -1401,7 +1423,6 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))
   a.wcc_inv = nullptr;
   a.xdist = nullptr;   // no expansion record in batches
   a.cascade_window = kCascadeLevels;
-
   load_policy(a, pol);
   for (;;) {
     if (vg.bid == 0 && threadIdx.x == 0)
@@ -1415,7 +1436,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))
     a.src = Q.src;
     a.P.max_iters = Q.g.n + 2;
     const bool sssp = Q.algo == 1;
-    a.cascade_after = b.cascade && Q.g.m < 8ll * Q.g.n && Q.g.m >= 4 ? (sssp ? kCascadeAfterSssp : kCascadeAfterBfs) : 0;
+    a.cascade_after = kCascade && cascade_graph(Q.g) ? (sssp ? kCascadeAfterSssp : kCascadeAfterBfs) : 0;
     init_state(vg, a, sssp);
     // the previous query's statistics were read before the barrier above
     if (vg.bid < (unsigned)kStatLines && threadIdx.x == 0) {
@@ -1432,8 +1453,15 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))
     if (vg.bid == 0 && threadIdx.x < 64) init_source(a, vg.nb);
     if (!bar.sync()) break;
     const unsigned long long mu0 = (unsigned long long)(Q.g.m - degree_of(Q.g.off, Q.src));
-    const bool ok = sssp ? batch_query<SsspOps>(vg, a, bar, lds, pol, cas.sssp, mu0)
-                         : batch_query<BfsOps>(vg, a, bar, lds, pol, cas.bfs, mu0);
+    bool ok;
+    if constexpr (kCascade) {
+      __shared__ union { LdsCas<true> sssp; LdsCas<false> bfs; } cas;
+      ok = sssp ? batch_query<SsspOps>(vg, a, bar, lds, pol, &cas.sssp, mu0)
+                : batch_query<BfsOps>(vg, a, bar, lds, pol, &cas.bfs, mu0);
+    } else {
+      ok = sssp ? batch_query<SsspOps, int>(vg, a, bar, lds, pol, nullptr, mu0)
+                : batch_query<BfsOps, int>(vg, a, bar, lds, pol, nullptr, mu0);
+    }
     if (vg.bid == 0 && threadIdx.x == 0) {
       BatchStat &r = b.stats[b.order[qi]];
       r.iterations = (int)load_relaxed(&C->stats.v[6]);
@@ -1558,10 +1586,11 @@ hipError_t weight_sum(const unsigned *w, long long m, unsigned long long *out, h
 
 hipError_t batch_launch(const BatchArgs &b, int grid, hipStream_t s) {
   hipLaunchKernelGGL(k_batch_reset, dim3(b.nteams), dim3(256), 0, s, b);
-  hipLaunchKernelGGL(k_batch, dim3(grid), dim3(kBlock), 0, s, b);
+  if (b.cascade) hipLaunchKernelGGL(k_batch<true>, dim3(grid), dim3(kBlock), 0, s, b);
+  else hipLaunchKernelGGL(k_batch<false>, dim3(grid), dim3(kBlock), 0, s, b);
   return hipGetLastError();
 }
 
-const void *batch_kernel() { return (const void *)k_batch; }
+const void *batch_kernel(bool cascade) { return cascade ? (const void *)k_batch<true> : (const void *)k_batch<false>; }
 
 }  // namespace sx

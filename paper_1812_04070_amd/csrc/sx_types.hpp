@@ -33,7 +33,7 @@ enum : unsigned { SX_ERR_NONE = 0, SX_ERR_DEADLOCK = 1, SX_ERR_OVERFLOW = 2, SX_
                   SX_ERR_INPUT = 4, SX_ERR_TAIL = 5 };
 
 // kernel exit reasons written to Ctrl::state
-enum : int { EXIT_NONE = 0, EXIT_DONE = 1, EXIT_SWITCH = 2, EXIT_ERROR = 3, EXIT_LIMIT = 4 };
+enum : int { EXIT_NONE = 0, EXIT_DONE = 1, EXIT_SWITCH = 2, EXIT_ERROR = 3, EXIT_LIMIT = 4, EXIT_CASCADE = 5 };
 
 // worklist bins (Section 4 step I: small / medium / large lists)
 enum : int { BIN_SMALL = 0, BIN_MED = 1, BIN_LARGE = 2, NBINS = 3 };
@@ -175,6 +175,9 @@ struct TravArgs {
 // levels a BFS step takes at most.
 constexpr int kCascadeAfterBfs = 8, kCascadeAfterSssp = 16;
 constexpr unsigned kCascadeLevels = 64;
+// Graphs whose runs may: fewer than 8 arcs per vertex (denser ones end before),
+// and the four arcs that the cascade reads at once.
+__host__ __device__ inline bool cascade_graph(const DevGraph &g) { return g.m < 8ll * g.n && g.m >= 4; }
 
 // Batched queries (see k_batch).
 struct BatchQuery {
@@ -198,7 +201,8 @@ struct BatchArgs {
   Params P;
   const float *mlp;
   BatchStat *stats;             // [nq]
-  int cascade;                  // 1: queries on sparse graphs may go over to the cascade
+  int cascade;                  // 1: queries on sparse graphs (cascade_graph; there are some)
+                                // may go over to the cascade
 };
 
 struct KArgs {
