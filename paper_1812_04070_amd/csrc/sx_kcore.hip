@@ -284,20 +284,25 @@ SX_DEV void kpeel_push(const VGrid &vg, const KArgs &a, int k, int j, const View
   // no atomic touches: plain loads of the current degrees, between the atomics
   // on the same lines, held both back (2^17 words: 10 G/s mixed, 27 G/s
   // atomics alone).  A target below k that is still alive costs an atomic.
-  // R-MAT s22: pushes of 50 us and more 9.1 -> 6.5 ms with kHotHits
+  // R-MAT s22: pushes of 50 us and more 9.1 -> 6.5 ms with kHotHits.  The row
+  // lengths are behind a branch: as selects per lane they lengthened the chain
+  // of a light step's cascade (path of 100,000 125 ms, 113 so; 1500^2 grid 1.03,
+  // 0.95).  Light steps reading the current degrees instead: 121, 1.00, and
+  // R-MAT s22 17.2 -> 18.7
   auto op = [&](const int *v, const int *u, const int *arc, const bool *ok) {
     (void)v; (void)arc;
     int row[kIlp], old[kIlp], du[kIlp];
     bool dec[kIlp], act[kIlp];
 #pragma unroll
     for (int r = 0; r < kIlp; ++r) dec[r] = ok[r] && a.core[u[r]] == -1;
+    if (use_hot) {
 #pragma unroll
-    for (int r = 0; r < kIlp; ++r) row[r] = use_hot && dec[r] ? total_degree(g, u[r]) : 0;
+      for (int r = 0; r < kIlp; ++r) row[r] = dec[r] ? total_degree(g, u[r]) : 0;
 #pragma unroll
-    for (int r = 0; r < kIlp; ++r) {
-      edges += ok[r] ? 1 : 0;
-      dec[r] = dec[r] && !(row[r] >= hot_deg && hot_add(u[r]));
+      for (int r = 0; r < kIlp; ++r) dec[r] = dec[r] && !(row[r] >= hot_deg && hot_add(u[r]));
     }
+#pragma unroll
+    for (int r = 0; r < kIlp; ++r) edges += ok[r] ? 1 : 0;
 #pragma unroll
     for (int r = 0; r < kIlp; ++r) old[r] = dec[r] ? atomic_sub_i32(&deg[u[r]], 1) : 0;
 #pragma unroll
