@@ -100,7 +100,7 @@ SX_DEV void bp_iteration(const BpArgs &a, int t, const Rows &rows, float *lf, fl
   const float2 *src2 = a.w.bpq[t & 1];
   const float *src = a.w.contrib[t & 1];
   constexpr int words = kMode == kBpStored ? 1 : 2, most = kHotBp / words;
-  const int nhot = a.g.n < most ? a.g.n : most;
+  const int nhot = hot_sources(a.g, most);
   const float *from = kMode == kBpStored ? src : (const float *)src2;
   for (int i = threadIdx.x; i < nhot * words; i += kPullBlock) hot[i] = from[i];
   __syncthreads();

@@ -171,7 +171,7 @@ template <bool kTrack>
 SX_DEV void pr_iteration(const PrArgs &a, int t, const Rows &rows, LdsPull &lds, float D, Track &tr, float *hot) {
   const Work &w = a.w;
   const float *src = w.contrib[t & 1];
-  const int nhot = a.g.n < kHotPr ? a.g.n : kHotPr;
+  const int nhot = hot_sources(a.g, kHotPr);
   stage_hot(hot, src, nhot);
   float *dst = w.contrib[(t + 1) & 1];
   const bool last = !kTrack && t == a.iters - 1;
