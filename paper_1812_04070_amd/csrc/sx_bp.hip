@@ -96,11 +96,10 @@ SX_DEV void bp_gather(CSum &s, const BpArgs &a, const float2 *src2, const float 
 // One iteration; `last` writes beliefs, else the next state (q alone from a
 // run that stores its couplings, else (q, deg)).
 template <int kMode>
-SX_DEV void bp_iteration(const BpArgs &a, int t, const Rows &rows, float *lf, float *hot) {
+SX_DEV void bp_iteration(const BpArgs &a, int t, const Rows &rows, float *lf, float *hot, int nhot) {
   const float2 *src2 = a.w.bpq[t & 1];
   const float *src = a.w.contrib[t & 1];
-  constexpr int words = kMode == kBpStored ? 1 : 2, most = kHotBp / words;
-  const int nhot = hot_sources(a.g, most);
+  constexpr int words = kMode == kBpStored ? 1 : 2;
   const float *from = kMode == kBpStored ? src : (const float *)src2;
   for (int i = threadIdx.x; i < nhot * words; i += kPullBlock) hot[i] = from[i];
   __syncthreads();
@@ -155,10 +154,11 @@ __global__ void __launch_bounds__(kPullBlock) k_bp_fused(BpArgs a) {
   if (!bar.sync()) return;
   const Rows rows = rows_place(vg, a.w, a.g.n, a.g.off, a.g.off, a.P, lds);
   if (!bar.sync()) return;
+  const int pairs = hot_sources(a.g, kHotBp / 2), single = hot_sources(a.g, kHotBp);
   for (int t = 0; t < a.iters; ++t) {
-    if (!a.couple) bp_iteration<kBpWeigh>(a, t, rows, lf, hot);
-    else if (t == 0) bp_iteration<kBpStore>(a, t, rows, lf, hot);
-    else bp_iteration<kBpStored>(a, t, rows, lf, hot);
+    if (!a.couple) bp_iteration<kBpWeigh>(a, t, rows, lf, hot, pairs);
+    else if (t == 0) bp_iteration<kBpStore>(a, t, rows, lf, hot, pairs);
+    else bp_iteration<kBpStored>(a, t, rows, lf, hot, single);
     if (!bar.sync()) return;
   }
   if (vg.bid == 0 && threadIdx.x == 0) {
