@@ -61,21 +61,21 @@ enum { kBpWeigh, kBpStore, kBpStored };
 // a vertex of degree len, kIlp arcs of a lane in flight, added in order.
 // Whole wavefronts; a place past the row's end adds zero (as in sx_pagerank.hip).
 template <int kMode>
-SX_DEV void bp_gather(CSum &s, const BpArgs &a, const float2 *src2, const float *src, int beg, int e0, int len,
-                      int stride, const float *hot, int nhot) {
+SX_DEV void bp_gather(CSum &s, const BpArgs &a, const float2 *src2, const float *src, int beg, unsigned e0, unsigned len,
+                      unsigned stride, const float *hot, int nhot) {
   const int *ii = a.g.idx;
   const float dv = (float)len;
-  for (int e = e0; ballot(e < len); e += kIlp * stride) {
+  for (unsigned e = e0; ballot(e < len); e += kIlp * stride) {
     int u[kIlp];
     float c[kIlp], q[kIlp];
 #pragma unroll
-    for (int r = 0; r < kIlp; ++r) {
-      const int at = beg + (e + r * stride < len ? e + r * stride : 0);
+    for (unsigned r = 0; r < kIlp; ++r) {
+      const int at = beg + (int)(e + r * stride < len ? e + r * stride : 0u);
       u[r] = ii[at];
       c[r] = kMode == kBpStored ? a.couple[at] : bp_theta(a.g.w, at);
     }
 #pragma unroll
-    for (int r = 0; r < kIlp; ++r) {
+    for (unsigned r = 0; r < kIlp; ++r) {
       const bool ok = e + r * stride < len;
       const int i = ok ? u[r] : 0;
       if constexpr (kMode == kBpStored) {
@@ -84,7 +84,7 @@ SX_DEV void bp_gather(CSum &s, const BpArgs &a, const float2 *src2, const float 
         const float2 x = i < nhot ? ((const float2 *)hot)[i] : src2[i];
         q[r] = x.x;
         c[r] = a.kappa * c[r] / fmaxf(x.y, dv);
-        if (kMode == kBpStore && ok) a.couple[beg + e + r * stride] = c[r];
+        if (kMode == kBpStore && ok) a.couple[beg + (int)(e + r * stride)] = c[r];
       }
       q[r] = ok ? c[r] * q[r] : 0.f;
     }
@@ -114,7 +114,7 @@ SX_DEV void bp_iteration(const BpArgs &a, int t, const Rows &rows, float *lf, fl
   for (unsigned i = rows.at[5] + blockIdx.x; i < rows.at[6]; i += gridDim.x) {
     const Row x = row_load(rows, i, rows.at[6]);
     CSum s{0.f, 0.f};
-    bp_gather<kMode>(s, a, src2, src, x.beg, (int)threadIdx.x, x.len, kPullBlock, hot, nhot);
+    bp_gather<kMode>(s, a, src2, src, x.beg, threadIdx.x, (unsigned)x.len, kPullBlock, hot, nhot);
     s = pull_merge1(s, lf);
     if (threadIdx.x == 0) finish(x, s);
   }
@@ -125,7 +125,7 @@ SX_DEV void bp_iteration(const BpArgs &a, int t, const Rows &rows, float *lf, fl
     constexpr int kLanes = decltype(lanes)::value;
     rows_walk<kLanes>(rows, cls, gw, nw, turn, [&](const Row &x, int sub) {
       CSum s{0.f, 0.f};
-      bp_gather<kMode>(s, a, src2, src, x.beg, sub, x.len, kLanes, hot, nhot);
+      bp_gather<kMode>(s, a, src2, src, x.beg, (unsigned)sub, (unsigned)x.len, kLanes, hot, nhot);
       s = lanes_merge<kLanes>(s);
       if (sub == 0 && x.v >= 0) finish(x, s);
     });

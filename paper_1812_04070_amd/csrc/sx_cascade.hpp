@@ -250,17 +250,17 @@ SX_DEV void cascade_step(const VGrid &vg, const TravArgs &a, LdsCas<kWeighted> &
         relax(len <= kCasLane && part < len, u, x.y, w, nx, count);
         if (ballot(len > 4) == 0) continue;
         for (int j = 4; ballot(len <= kCasLane && j < len); j += 4) {
-          const int e = (int)x.z + j + part;
-          const bool ok = len <= kCasLane && e < (int)x.w;
+          const bool ok = len <= kCasLane && j + part < len;
+          const int e = ok ? (int)x.z + j + part : 0;
           relax(ok, ok ? idx[e] : 0, x.y, kWeighted && ok ? wt[e] : 1u, nx, count);
         }
         for (uint64_t rows = ballot(part == 0 && len > kCasLane); rows; rows &= rows - 1) {
           const int src = __ffsll((long long)rows) - 1;
           const int rb = __shfl((int)x.z, src), re = __shfl((int)x.w, src);
           const unsigned d = __shfl(x.y, src);
-          for (int e0 = rb; e0 < re; e0 += 64) {
-            const int e = e0 + lane_id();
-            const bool ok = e < re;
+          for (unsigned e0 = (unsigned)rb; e0 < (unsigned)re; e0 += 64u) {
+            const unsigned e = e0 + (unsigned)lane_id();
+            const bool ok = e < (unsigned)re;
             relax(ok, ok ? idx[e] : 0, d, kWeighted && ok ? wt[e] : 1u, nx, count);
           }
         }

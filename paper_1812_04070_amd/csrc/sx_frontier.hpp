@@ -562,7 +562,9 @@ SX_DEV void visit_small(int n, Acc item, unsigned cnt, const int *off, const int
   }
 }
 
-// Medium bin: one wavefront per vertex, 64 * kIlp arcs per step.
+// Medium bin: one wavefront per vertex, 64 * kIlp arcs per step.  (Here and
+// wherever a step may pass a row's end: arcs are counted unsigned, as the last
+// row may end within a step of 2^31.)
 template <class Acc, class Op>
 SX_DEV void visit_med(int n, Acc item, unsigned cnt, const int *off, const int *idx, Op &op,
                       unsigned gw, unsigned nwaves) {
@@ -571,13 +573,14 @@ SX_DEV void visit_med(int n, Acc item, unsigned cnt, const int *off, const int *
     const int v = item(i);
     if ((unsigned)v >= (unsigned)n) continue;
     const int beg = off[v], end = off[v + 1];
-    for (int a = beg; a < end; a += 64 * kIlp) {
+    for (unsigned a = (unsigned)beg; a < (unsigned)end; a += 64u * kIlp) {
       int vv[kIlp], u[kIlp], arc[kIlp];
       bool ok[kIlp];
 #pragma unroll
       for (int r = 0; r < kIlp; ++r) {
-        arc[r] = a + r * 64 + lane;
-        ok[r] = arc[r] < end;
+        const unsigned e = a + (unsigned)(r * 64 + lane);
+        arc[r] = (int)e;
+        ok[r] = e < (unsigned)end;
         vv[r] = v;
         u[r] = ok[r] ? idx[arc[r]] : 0;
       }
@@ -600,13 +603,14 @@ SX_DEV void visit_large(const VGrid &vg, int n, Acc item, unsigned cnt, const in
     const long long b0 = (long long)vb + (long long)c * chunk;
     const int beg = (int)(b0 < ve ? b0 : ve);
     const int end = (int)((b0 + chunk) < ve ? (b0 + chunk) : ve);
-    for (int a = beg; a < end; a += kBlock * kIlp) {
+    for (unsigned a = (unsigned)beg; a < (unsigned)end; a += (unsigned)(kBlock * kIlp)) {
       int vv[kIlp], u[kIlp], arc[kIlp];
       bool ok[kIlp];
 #pragma unroll
       for (int r = 0; r < kIlp; ++r) {
-        arc[r] = a + r * kBlock + (int)threadIdx.x;
-        ok[r] = arc[r] < end;
+        const unsigned e = a + (unsigned)(r * kBlock) + threadIdx.x;
+        arc[r] = (int)e;
+        ok[r] = e < (unsigned)end;
         vv[r] = v;
         u[r] = ok[r] ? idx[arc[r]] : 0;
       }

@@ -393,7 +393,7 @@ SX_DEV void kpeel_pull(const VGrid &vg, const KArgs &a, int k, int j, const View
   auto count_row = [&](const int *idx, int beg, int end) {
     int c = 0;
     int e = beg;
-    for (; e + 4 <= end; e += 4) {
+    for (; end - e >= 4; e += 4) {
       const int u0 = idx[e], u1 = idx[e + 1], u2 = idx[e + 2], u3 = idx[e + 3];
       c += (stamp[u0] == j) + (stamp[u1] == j) + (stamp[u2] == j) + (stamp[u3] == j);
     }
@@ -438,7 +438,7 @@ SX_DEV void kpeel_pull(const VGrid &vg, const KArgs &a, int k, int j, const View
       const int *off = pass ? g.in_off : g.off;
       const int *idx = pass ? g.in_idx : g.idx;
       const int beg = off[v], end = off[v + 1];
-      for (int e = beg + lane; e < end; e += 64) {
+      for (unsigned e = (unsigned)beg + (unsigned)lane; e < (unsigned)end; e += 64u) {
         c += stamp[idx[e]] == j;
         ++edges;
       }

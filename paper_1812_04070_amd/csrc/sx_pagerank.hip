@@ -122,15 +122,15 @@ SX_DEV void stage_hot(float *hot, const float *src, int nhot) {
 // gathers of a lane in flight.  Whole wavefronts; a place past the row's end
 // reads the row's first id and adds zero, which changes neither part of a
 // compensated sum.
-SX_DEV void gather(CSum &s, const float *src, const int *ii, int beg, int e0, int len, int stride,
+SX_DEV void gather(CSum &s, const float *src, const int *ii, int beg, unsigned e0, unsigned len, unsigned stride,
                    const float *hot, int nhot) {
-  for (int e = e0; ballot(e < len); e += kIlp * stride) {
+  for (unsigned e = e0; ballot(e < len); e += kIlp * stride) {
     int u[kIlp];
     float x[kIlp];
 #pragma unroll
-    for (int r = 0; r < kIlp; ++r) u[r] = ii[beg + (e + r * stride < len ? e + r * stride : 0)];
+    for (unsigned r = 0; r < kIlp; ++r) u[r] = ii[beg + (int)(e + r * stride < len ? e + r * stride : 0u)];
 #pragma unroll
-    for (int r = 0; r < kIlp; ++r) {
+    for (unsigned r = 0; r < kIlp; ++r) {
       const bool ok = e + r * stride < len;
       const int i = ok ? u[r] : 0;
       x[r] = i < nhot ? hot[i] : src[i];
@@ -226,7 +226,7 @@ SX_DEV void pr_iteration(const PrArgs &a, int t, const Rows &rows, LdsPull &lds,
     const Row x = row_load(rows, i, rows.at[6]);
     CSum s{0.f, 0.f};
     if (x.len > kLongRow) gather_long(s, src, ii, x.beg, threadIdx.x, (unsigned)x.len, hot, nhot);
-    else gather(s, src, ii, x.beg, (int)threadIdx.x, x.len, kPullBlock, hot, nhot);
+    else gather(s, src, ii, x.beg, threadIdx.x, (unsigned)x.len, kPullBlock, hot, nhot);
     s = pull_merge1(s, lds.f);
     if (threadIdx.x == 0) finish(x, s);
   }
@@ -237,7 +237,7 @@ SX_DEV void pr_iteration(const PrArgs &a, int t, const Rows &rows, LdsPull &lds,
     constexpr int kLanes = decltype(lanes)::value;
     rows_walk<kLanes>(rows, cls, gw, nw, turn, [&](const Row &x, int sub) {
       CSum s{0.f, 0.f};
-      gather(s, src, ii, x.beg, sub, x.len, kLanes, hot, nhot);
+      gather(s, src, ii, x.beg, (unsigned)sub, (unsigned)x.len, kLanes, hot, nhot);
       s = lanes_merge<kLanes>(s);
       if (sub == 0 && x.v >= 0) finish(x, s);
     });
@@ -347,9 +347,9 @@ SX_DEV void pr_push_step(const PrArgs &a, int j, const ViewRef &V, const Totals 
     if (threadIdx.x == 0) lds.share = take(v, end - beg);
     __syncthreads();
     const float share = lds.share;
-    for (int e0 = beg; e0 < end; e0 += kBlock) {
-      const int e = e0 + (int)threadIdx.x;
-      const bool ok = e < end;
+    for (unsigned e0 = (unsigned)beg; e0 < (unsigned)end; e0 += kBlock) {
+      const unsigned e = e0 + threadIdx.x;
+      const bool ok = e < (unsigned)end;
       send(ok, ok ? idx[e] : 0, share);
     }
     __syncthreads();
@@ -364,9 +364,9 @@ SX_DEV void pr_push_step(const PrArgs &a, int j, const ViewRef &V, const Totals 
     float share = 0.f;
     if (lane == 0) share = take(v, end - beg);
     share = __shfl(share, 0);
-    for (int e0 = beg; e0 < end; e0 += 64) {
-      const int e = e0 + lane;
-      const bool ok = e < end;
+    for (unsigned e0 = (unsigned)beg; e0 < (unsigned)end; e0 += 64u) {
+      const unsigned e = e0 + (unsigned)lane;
+      const bool ok = e < (unsigned)end;
       send(ok, ok ? idx[e] : 0, share);
     }
   }

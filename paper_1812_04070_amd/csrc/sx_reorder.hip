@@ -60,7 +60,7 @@ __global__ void k_rk_rows(const int *off, const int *idx, const unsigned *w, con
     const int v = perm[i];
     const int beg = off[v], end = off[v + 1];
     const int out = noff[i];
-    for (int e = beg + lane; e < end; e += 64) {
+    for (long long e = (long long)beg + lane; e < end; e += 64) {
       nidx[out + (e - beg)] = inv[idx[e]];
       if (w) nw[out + (e - beg)] = w[e];
     }

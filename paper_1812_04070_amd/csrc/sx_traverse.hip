@@ -459,16 +459,16 @@ SX_PHASE void pull_phase(const VGrid &vg, const TravArgs &a, const Params &P, in
     unsigned best = 0xFFFFFFFFu;
     if (!Ops::kVote) best = dist[v];
     bool found = false;
-    for (int b = beg; b < end; b += kBlock) {
-      const int arc = b + (int)threadIdx.x;
+    for (unsigned b = (unsigned)beg; b < (unsigned)end; b += kBlock) {
+      const unsigned arc = b + threadIdx.x;
       bool hit = false;
-      if (arc < end) {
+      if (arc < (unsigned)end) {
         ++edges;
         const int u = g.in_idx[arc];
         if (fbit(fb, u)) {
           hit = true;
           if (!Ops::kVote) {
-            const unsigned c = pull_offer<Ops>(dist, g, u, arc, err);
+            const unsigned c = pull_offer<Ops>(dist, g, u, (int)arc, err);
             best = c < best ? c : best;
           }
         }
@@ -520,7 +520,7 @@ SX_PHASE void pull_phase(const VGrid &vg, const TravArgs &a, const Params &P, in
     int arc = beg;
     if (mg > 1) {
       const int stop = end - beg > kVoteFirst ? beg + kVoteFirst : end;
-      for (; !act && arc + 4 <= stop; arc += 4) {
+      for (; !act && stop - arc >= 4; arc += 4) {
         const int u0 = g.in_idx[arc], u1 = g.in_idx[arc + 1], u2 = g.in_idx[arc + 2], u3 = g.in_idx[arc + 3];
         edges += 4;
         act = fbit(fb, u0) | fbit(fb, u1) | fbit(fb, u2) | fbit(fb, u3);
@@ -530,10 +530,10 @@ SX_PHASE void pull_phase(const VGrid &vg, const TravArgs &a, const Params &P, in
       const int l = __ffsll((long long)left) - 1;
       const int b0 = __shfl(arc, l), e0 = __shfl(end, l);
       bool found = false;
-      for (int e = b0; !found && e < e0; e += 64) {
-        const bool ok = e + lane < e0;
+      for (unsigned e = (unsigned)b0; !found && e < (unsigned)e0; e += 64u) {
+        const bool ok = e + (unsigned)lane < (unsigned)e0;
         edges += ok ? 1 : 0;
-        found = ballot(ok && fbit(fb, g.in_idx[ok ? e + lane : e])) != 0;
+        found = ballot(ok && fbit(fb, g.in_idx[ok ? e + (unsigned)lane : e])) != 0;
       }
       if (lane == l) act = found;
     }
@@ -546,11 +546,11 @@ SX_PHASE void pull_phase(const VGrid &vg, const TravArgs &a, const Params &P, in
     if ((unsigned)v >= (unsigned)g.n) continue;
     const int beg = g.in_off[v], end = g.in_off[v + 1];
     unsigned best = 0xFFFFFFFFu;
-    for (int arc = beg + lane; arc < end; arc += 64) {
+    for (unsigned arc = (unsigned)beg + (unsigned)lane; arc < (unsigned)end; arc += 64u) {
       ++edges;
       const int u = g.in_idx[arc];
       if (fbit(fb, u)) {
-        const unsigned c = pull_offer<Ops>(dist, g, u, arc, err);
+        const unsigned c = pull_offer<Ops>(dist, g, u, (int)arc, err);
         best = c < best ? c : best;
       }
     }
@@ -577,7 +577,7 @@ SX_PHASE void pull_phase(const VGrid &vg, const TravArgs &a, const Params &P, in
         d = end - beg;
         int arc = beg;
         if (Ops::kVote) {
-          for (; arc + 4 <= end; arc += 4) {
+          for (; end - arc >= 4; arc += 4) {
             const int u0 = g.in_idx[arc], u1 = g.in_idx[arc + 1], u2 = g.in_idx[arc + 2],
                       u3 = g.in_idx[arc + 3];
             edges += 4;
@@ -591,7 +591,7 @@ SX_PHASE void pull_phase(const VGrid &vg, const TravArgs &a, const Params &P, in
         } else {
           unsigned best = dist[v];
           const unsigned old = best;
-          for (; arc + 4 <= end; arc += 4) {
+          for (; end - arc >= 4; arc += 4) {
             int u[4];
             bool h[4];
 #pragma unroll

@@ -177,8 +177,8 @@ __global__ void __launch_bounds__(kBlock) k_wcc_link(WccArgs a) {
     int beg = 0, end = 0;
     if (v < n && par_load(&a.par[v]) != skip) {
       end = a.g.off[v + 1];
-      beg = a.g.off[v] + from;
-      if (beg > end) beg = end;
+      beg = a.g.off[v];
+      beg = end - beg > from ? beg + from : end;
     }
     const int len = end - beg;
     edges += len;
@@ -189,7 +189,7 @@ __global__ void __launch_bounds__(kBlock) k_wcc_link(WccArgs a) {
     for (uint64_t rows = ballot(len >= kWccWaveRow && len < kWccGroupRow); rows; rows &= rows - 1) {
       const int r = __ffsll((long long)rows) - 1;
       const int x = __shfl((int)v, r), b = __shfl(beg, r), f = __shfl(end, r);
-      for (int e = b + lane; e < f; e += 64) link(a.par, x, idx[e]);
+      for (unsigned e = (unsigned)(b + lane); e < (unsigned)f; e += 64u) link(a.par, x, idx[e]);
     }
     __syncthreads();
     for (int h = 0; h < hubs; ++h) {
