@@ -1105,6 +1105,8 @@ SX_DEV void cascade_enter(const VGrid &vg, const TravArgs &a, const RunState &s,
 // Returns whether the launch ran a phase of an active run.
 template <class Ops, bool kCascade>
 SX_DEV bool seq_body(const TravArgs &a, unsigned L, LdsTrav &lds, LdsPolicy &pol) {
+  // whether lists may come from a scan that no decision preceded (see [11])
+  constexpr bool kSettle = kCascade || std::is_same<Ops, SsspOps>::value;
   Ctrl *C = a.w.ctrl;
   const VGrid vg = hw_grid();
   Line &out = C->seq[(L + 1) & 1];
@@ -1124,7 +1126,7 @@ SX_DEV bool seq_body(const TravArgs &a, unsigned L, LdsTrav &lds, LdsPolicy &pol
   unsigned rebuilt = in[12];
   s.B = in[13] ? in[13] : (a.P.delta && a.P.delta_after == 0 ? a.P.delta : 0xFFFFFFFFu);
   s.dropped = in[14];
-  s.hold = (int)in[15];
+  if (kCascade) s.hold = (int)in[15];
   if (phase >= SEQ_DONE) {
     if (lead) seq_store(out, phase, s, pulling, 0, rebuilt);
     return false;
@@ -1208,7 +1210,7 @@ SX_DEV bool seq_body(const TravArgs &a, unsigned L, LdsTrav &lds, LdsPolicy &pol
         T = make_view(vg, a, rebuilt ? SLOT_SCAN : it % 3, it & 1, lds, ref);
         if (rebuilt && !scan_fits(a, T)) break;
       }
-      if (due == 2) {
+      if (kSettle && due == 2) {
         // after a marking step or the cascade: the end, and the counts that a
         // later decision goes by (the direction is not open, see mark)
         if (T.nf == 0 || s.it >= a.P.max_iters) {
@@ -1235,7 +1237,7 @@ SX_DEV bool seq_body(const TravArgs &a, unsigned L, LdsTrav &lds, LdsPolicy &pol
       // rebuild the lists of it+1, then push them
       ballot_next(vg, a, s.P, ops, it, lds);
       ++s.it;
-      if (lead) seq_store(out, PH_PUSH, s, 0, due >= 2 ? 2 : 0, 1);
+      if (lead) seq_store(out, PH_PUSH, s, 0, kSettle && due >= 2 ? 2 : 0, 1);
       break;
     case PH_PULL_SCAN:
       if (lead) atomic_add_u32(&C->stats.v[6], 1u);
