@@ -147,7 +147,9 @@ sx_status sx_graph_info(const sx_graph *g, int32_t *n, int64_t *m, int32_t *dire
  *              return (FP32 arithmetic, compensated sums).  Undirected
  *              graphs only (SX_EUNSUPPORTED otherwise); pass source -1.
  *              The first run of several iterations on a graph adds 4 bytes
- *              an arc to its workspace, if the device has them. */
+ *              an arc to its workspace, freed with the graph, if that is at
+ *              most an eighth of the device memory then free; otherwise the
+ *              run takes longer. */
 typedef enum { SX_BFS = 0, SX_SSSP = 1, SX_KCORE = 2, SX_PAGERANK = 3, SX_WCC = 4, SX_BP = 5 } sx_algo;
 
 /* sssp_delta: bucket width of delta-stepping for SX_SSSP (Section 3.3: the

@@ -117,7 +117,6 @@ struct sx_graph {
   unsigned *d_xdist = nullptr;  // SSSP / WCC expansion record (TravArgs::xdist)
   void *state = nullptr;
   float *d_couple = nullptr;    // belief propagation: the arcs' couplings
-  bool no_couple = false;       // there was no memory for them
   long long weight_sum = -1;  // sum of the arc weights, once SX_DELTA_AUTO needed it
   // where the lists of the next iteration sit after sx_run_iterations:
   // record slot, region parity, run grid (-1: no such run yet)
@@ -1397,15 +1396,19 @@ static sx_status run_bp(sx_program *p, sx_graph *G, void *d_belief, hipStream_t 
   a.iters = p->ap.bp_iters;
   // several iterations share the arcs' couplings through an array the graph
   // keeps from its first such run on (4 bytes an arc; the values are each
-  // run's own); where it cannot be had, every iteration weighs its arcs
-  if (a.iters > 1 && G->g.m > 0 && !G->d_couple && !G->no_couple) {
+  // run's own), if it takes no more than an eighth of the memory that is free: a
+  // program that has filled the device keeps what it left.  Without it every
+  // iteration weighs its arcs.
+  if (a.iters > 1 && G->g.m > 0 && !G->d_couple) {
+    const size_t bytes = sizeof(float) * (size_t)G->g.m;
+    size_t free_bytes = 0, total = 0;
     void *c = nullptr;
-    if (hipMalloc(&c, sizeof(float) * (size_t)G->g.m) == hipSuccess) {
+    if (hipMemGetInfo(&free_bytes, &total) == hipSuccess && bytes <= free_bytes / 8 &&
+        hipMalloc(&c, bytes) == hipSuccess) {
       G->owned.push_back(c);
       G->d_couple = (float *)c;
     } else {
       (void)hipGetLastError();
-      G->no_couple = true;
     }
   }
   a.couple = a.iters > 1 ? G->d_couple : nullptr;
