@@ -165,8 +165,8 @@ typedef enum { SX_BFS = 0, SX_SSSP = 1, SX_KCORE = 2, SX_PAGERANK = 3, SX_WCC = 
  * value; it changes the work and the iteration count only.  Used by the
  * sequenced arrangement (SX_FUSE_AUTO / SX_SEQUENCED); the persistent and
  * unfused arrangements and batches relax without buckets (a batch under a
- * policy that fixes nothing widens its steps by itself, see fused), and a run that
- * switches to pull steps drops the buckets from then on. */
+ * policy that fixes nothing takes windows of 8 mean weights by itself, see
+ * fused), and a run that switches to pull steps drops the buckets from then on. */
 typedef struct {
   sx_algo algo;
   float pr_damping;      /* PageRank damping d (0.85)                          */
@@ -223,8 +223,10 @@ void sx_program_destroy(sx_program *p);
  *             (sequenced for BFS, SSSP and k-core, fused for PageRank; with
  *             every other field but policy 0 too, a BFS, or an SSSP with buckets, on a
  *             graph of fewer than 8 arcs per vertex goes over to launches
- *             that each advance it by a window of distances once its
- *             frontier stays light: same results, and for BFS the same
+ *             that each advance it by a window of distances (for SSSP the
+ *             bucket width, at most 8 mean weights) once its
+ *             frontier stays light, and back to the phases where its lists
+ *             grow long: same results, and for BFS the same
  *             iteration count, the levels; so do a batch's queries;
  *             and a BFS, or an SSSP without buckets, of up to 24,576
  *             vertices and few arcs is one launch of one workgroup)
@@ -291,7 +293,8 @@ typedef struct {
 /* Run program p on graph g.  source: start vertex (BFS, SSSP), ignored (pass
  * -1) for k-core and PageRank.  d_out: caller-owned device array of n
  * elements (int32 depth | uint32 dist | int32 core | float rank).  Blocks the
- * host until the run is complete.  stats may be NULL.
+ * host until the run is complete.  stats may be NULL.  A run that fails may
+ * have used d_out for its state; on a renumbered graph it leaves d_out alone.
  * Errors: SX_EINVAL (source out of range, SSSP on an unweighted graph, wrong
  * d_out), SX_EDEADLOCK, SX_EOVERFLOW, SX_EHIP. */
 sx_status sx_run(sx_program *p, const sx_graph *g, int32_t source, void *d_out,

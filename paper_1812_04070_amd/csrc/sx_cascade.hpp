@@ -21,15 +21,15 @@
 //
 // Bound: a round's chain of an LDS queue read, the neighbour's row offsets
 // beside the atomic minimum, its first four ids (read for every neighbour, so
-// that the queue entry carries them, in one unguarded load: a branch per id
-// made the compiler wait for the minimum first, 5.7 ms against 5.1 below), and
+// that the queue entry carries them, in one load without a branch per id, which
+// the compiler would put behind the minimum), and
 // the append; and the instructions around it.  So an entry has four lanes, an
 // arc each: with four arcs to a lane, whose appends follow one another, a
 // round took 3.5 us against 1.2.  2048^2 grid BFS: 49.7 ms in levels, 5.1 here
-// (before the one load 5.2; workgroups of 64 / 128 / 512 threads 6.0 / 5.3 /
+// (ids read when the entry is expanded 5.2; workgroups of 64 / 128 / 512 threads 6.0 / 5.3 /
 // 6.0; 16 or 32 listed vertices a workgroup 5.5 / 5.9; 16, 32, 128 levels a
-// step 7.1 / 5.9 / 5.3); 4096^2 grid SSSP 167 -> 22.1 (before the one load
-// 24.3; window 4 / 6 / 20 mean weights: 32 / 27 / 34).  Reading an entry's
+// step 7.1 / 5.9 / 5.3); 4096^2 grid SSSP 167 -> 21.6 (ids read when the entry is
+// expanded 24.3; window 4 / 6 / 20 mean weights: 32 / 27 / 34).  Reading an entry's
 // distance again before expanding it saved a quarter of the arcs and no time.
 // In a batch (a step per team barrier), 48 queries over 8 R-MAT graphs of
 // scale 12-17 and grids of side 128 and 512: 20.0 -> 3.8 ms.
@@ -45,8 +45,10 @@
 // (cas_way_back): it has met a part of the graph of low diameter, where a
 // window of unsynchronised relaxations does most of its work many times over.
 // Random graph of 3 M vertices and 6 arcs each behind a path of 20: BFS in
-// phases alone 0.94 ms, without the way back for lists with leftovers 5.0, with
-// it 1.1; SSSP (window of 8 mean weights) 3.0 / 11.1 / 3.7.
+// phases alone 0.92 ms, in the cascade to its end 4.9, with the way back 1.24
+// (the step that meets the blob, and launches enqueued for the cascade that then
+// find nothing to do); SSSP of 8 mean weights a bucket 3.0 / 10.8 / 2.9.  Behind a
+// path of 600: BFS 13.6 / 9.4 / 3.0, SSSP 21.1 / 16.2 / 6.5.
 #pragma once
 
 #include "sx_frontier.hpp"

@@ -71,9 +71,11 @@ constexpr int kLocalQ = 2048;
 constexpr unsigned kLocalArcs = 8192, kLocalArcsLight = 16384;   // per workgroup and step
 // Pull when the step's arcs exceed the alive arcs / alpha: pull steps read the
 // alive rows and one stamp per arc at ~100 G arcs/s, push steps reach 40-80
-// G arcs/s of their own rows (their dead and summed targets included).  R-MAT
-// s22, whole run: alpha 8 17.2 ms, 5 and 3.5 16.5, 2 16.3, 0.5 16.5; 16 and more 17.8
-// to 21.8.
+// G arcs/s of their own rows (their dead and summed targets included).  Whole
+// runs, alpha 2 / 3 / 4 / 6: R-MAT s22 17.13 / 17.29 / 17.24 / 17.61 ms, s20 9.05 /
+// 9.12 / 9.10 / 9.15 (runs differ by 0.05), a random graph of 2^20 vertices and 16
+// arcs each 1.30 / 1.30 / 1.24 / 1.24: 4 is the largest before s22 slows down, the
+// smallest before the random graph does.  16 and more on s22: 17.8 to 21.8.
 constexpr float kPullAlpha = 4.f;
 
 struct LdsK {

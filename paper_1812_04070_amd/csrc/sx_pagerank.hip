@@ -10,9 +10,10 @@
 //            iteration so that each arc costs one gather.
 //   Combine  sum over the in-arcs (aggregation), single writer per vertex.
 //
-// Task management: all vertices are active, so the binned lists are built by
-// one ballot-filter pass before the first iteration (the paper observes
-// PageRank needs the ballot filter exactly once) and reused.  Every sum --
+// Task management: all vertices are active, so their rows are classed by
+// length and written out as records by one ballot pass before the first
+// iteration (the paper observes PageRank needs the ballot filter exactly once;
+// sx_rows.hpp) and walked class by class in every one.  Every sum --
 // per vertex over its in-arcs, and the dangling mass over vertices -- is a
 // compensated (TwoSum) FP32 summation in a fixed order, so the result is
 // reproducible bit for bit and its error stays near the rounding of the
