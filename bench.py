@@ -164,6 +164,8 @@ def trav_kernel_name(kind: str, fused: int, arcs: int, n: int) -> str:
         return "k_wcc_* (hooking)"
     if kind == "kcore":
         return "k_kcore_seq" if seq else "k_kcore_fused"
+    if kind in ("bfs", "sssp") and fused == 0 and arcs < 8 * n:
+        return "k_cascade"   # takes the run over from the phases
     ops = {"bfs": "BfsOps", "wcc": "WccOps"}.get(kind, "SsspOps")
     if not seq:
         return f"k_fused<{ops}>"
