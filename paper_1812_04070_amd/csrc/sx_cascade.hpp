@@ -45,10 +45,9 @@
 // (cas_way_back): it has met a part of the graph of low diameter, where a
 // window of unsynchronised relaxations does most of its work many times over.
 // Random graph of 3 M vertices and 6 arcs each behind a path of 20: BFS in
-// phases alone 0.92 ms, in the cascade to its end 4.9, with the way back 1.24
-// (the step that meets the blob, and launches enqueued for the cascade that then
-// find nothing to do); SSSP of 8 mean weights a bucket 3.0 / 10.8 / 2.9.  Behind a
-// path of 600: BFS 13.6 / 9.4 / 3.0, SSSP 21.1 / 16.2 / 6.5.
+// phases alone 0.92 ms, in the cascade to its end 4.9, with the way back 0.86;
+// SSSP of 8 mean weights a bucket 3.0 / 10.8 / 2.7.  Behind a path of 600: BFS 13.6 /
+// 9.4 / 2.0, SSSP 21.1 / 16.2 / 6.0.
 #pragma once
 
 #include "sx_frontier.hpp"
@@ -226,13 +225,21 @@ SX_DEV void cascade_step(const VGrid &vg, const TravArgs &a, LdsCas<kWeighted> &
   };
   unsigned round = 0;
   // rounds until the queue is empty: queue round & 1 is read, the other one
-  // filled; its counter is round % 3
+  // filled; its counter is round % 3.  A grid of workgroups stops at a round that
+  // overflows the queue: of its 64 listed vertices at most no mesh makes so many,
+  // and the workgroup would walk a blob alone until the window's end (the step
+  // that meets one of 3 M vertices 387 us; with it the BFS above 1.24 ms).  A
+  // team's lists are longer.
+  constexpr bool kStopFull = kThreads == kCasBlock;
   auto drain = [&]() {
-    for (;; ++round) {
+    // (0 and too many in one comparison; the first round may be any number)
+    unsigned most = 0xFFFFFFFFu;
+    for (;; ++round, most = kStopFull ? (unsigned)kCasQ : most) {
       const int cur = (int)(round & 1u), nx = cur ^ 1;
-      const unsigned have = S.qn[round % 3] < (unsigned)kCasQ ? S.qn[round % 3] : (unsigned)kCasQ;
+      const unsigned filled = S.qn[round % 3];
+      if (filled - 1u >= most) break;
+      const unsigned have = filled < (unsigned)kCasQ ? filled : (unsigned)kCasQ;
       unsigned *count = &S.qn[(round + 1) % 3];
-      if (have == 0) break;
       ents += have;
       if (t == 0) S.qn[(round + 2) % 3] = 0u;
       // four lanes an entry, an arc each
@@ -304,6 +311,15 @@ SX_DEV void cascade_step(const VGrid &vg, const TravArgs &a, LdsCas<kWeighted> &
     }
     __syncthreads();
     drain();
+    if (kStopFull && S.qn[round % 3] != 0u) {
+      // stopped: what the queue holds is listed like what it had no room for
+      __syncthreads();
+      for (unsigned i = (unsigned)t; i < (unsigned)kCasQ; i += kThreads) {
+        const uint4 x = S.q[round & 1u][i];
+        list_append(true, (int)x.x, x.y, (int)(x.w - x.z));
+      }
+      if (t == 0) S.qn[round % 3] = 0u;
+    }
     __syncthreads();
   }
   // this workgroup's part of the next list
