@@ -1406,8 +1406,8 @@ SX_DEV bool batch_query(const VGrid &vg, const TravArgs &a, GridBarrier &bar, Ld
 // kCascade: some query's graph is sparse enough for the cascade.  Batches of
 // dense graphs run without its code, which costs registers that every phase has
 // to spill (64 SSSP queries on R-MAT s12 / s15 / s17: with it inside the phases'
-// loop, 316 registers spilled, 2.65 / 5.39 / 13.5 ms; without, 139 spilled, 2.60 /
-// 4.86 / 11.9).  With it, beside that loop, 174 are spilled.
+// loop, 316 registers spilled, 2.65 / 5.39 / 13.5 ms; without, 143 spilled, 2.60 /
+// 4.86 / 11.9).  With it, beside that loop, 170 are spilled.
 template <bool kCascade>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) k_batch(BatchArgs b) {
   __shared__ LdsTrav lds;
